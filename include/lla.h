@@ -306,8 +306,8 @@ lla_status lla_prefill_workspace_bytes(int dtype, int B, int H, int M, int d_hea
  *   scale    softmax scale, the teacher's 1/sqrt(d_head)
  *   other arguments as for lla_decode_attn; the workspace is the one sized by
  *   lla_decode_workspace_bytes (the context may be split over workgroups).
- * bf16 with d_head = 128 and r_k <= 256 runs on bf16 MFMA (fp32 accumulation,
- * keys reconstructed exactly from bf16 operands); fp32 and other shapes run a
+ * bf16 with d_head = 128 runs on bf16 MFMA (fp32 accumulation, keys
+ * reconstructed exactly from bf16 operands); fp32 and other head widths run a
  * plain fp32 kernel.
  * Errors: LLA_ERR_INVALID_ARG, LLA_ERR_WORKSPACE, LLA_ERR_HIP.
  */

@@ -573,7 +573,7 @@ lla_status lla_decode_attn_fullrope(int dtype, int out_dtype, int B, int H, int 
   // Split the context only for the MFMA kernel and only when the (b, h) units
   // alone leave compute units without a resident workgroup; every split keeps
   // at least 4 pages (the prologue forms the rotation constants and loads U_k).
-  if (workspace && lla::fullrope_mfma_ok(dtype, d_head, r_k, r_v)) {
+  if (workspace && lla::fullrope_mfma_ok(dtype, d_head)) {
     static const int forced = env_int("LLA_FULLROPE_SPLITS");
     const long target = (long)lla::fullrope_occupancy(r_k, r_v) * lla::device_cu_count();
     const long units = (long)B * H;

@@ -104,6 +104,28 @@ def test_bf16_ragged(r_k, r_v, N):
         _tight(f64(out), ref, tag)
 
 
+@pytest.mark.parametrize("r_k,r_v", [(257, 8), (288, 480), (300, 130), (321, 512), (384, 260), (385, 64), (512, 512)])
+@pytest.mark.parametrize("N,means", [(1, True), (130, False), (1500, True)])
+def test_bf16_ranks_above_256(r_k, r_v, N, means):
+    """U_k held in registers: every K-step bucket and both ends of it, value rows
+    in every bucket, ranks that are not multiples of 8, one page to several
+    splits, unequal lengths and explicit query positions."""
+    B, n_max = 2, ((N + 63) // 64) * 64 + 64
+    log(f"fullrope bf16 r=({r_k},{r_v}) N={N} means={means}")
+    ck, cv, q, uk, uv, muk, muv, pk, pv = _case(SMALL, r_k, r_v, B, N, n_max, 0, 1, means, torch.bfloat16)
+    lens, qp = [N, (N + 1) // 2], [N - 1, 3 * N]
+    ref = _oracle(q, ck, cv, uk, uv, muk, muv, ctx_len=lens, q_pos=qp)
+    ctx = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    qpos = torch.tensor(qp, dtype=torch.int32, device=DEV)
+    for w in (None, lla.new_workspace(B, SMALL.H, r_v, N)):
+        out = lla.decode_attn_fullrope(q, pk, pv, uk, uv, n_ctx=N, ctx_len=ctx, q_pos=qpos, mu_k=muk, mu_v=muv,
+                                       workspace=w)
+        torch.cuda.synchronize()
+        tag = f"ws={'yes' if w is not None else 'no'}"
+        assert_close(f64(out), ref, torch.bfloat16, tag)
+        _tight(f64(out), ref, tag)
+
+
 def test_bf16_long_context_split_positions_bf16_out():
     B, N, n_max = 2, 5000, 5056
     ck, cv, q, uk, uv, muk, muv, pk, pv = _case(SMALL, 192, 320, B, N, n_max, 0, 2, False, torch.bfloat16)
