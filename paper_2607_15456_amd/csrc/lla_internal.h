@@ -117,7 +117,7 @@ struct Prefill2dArgs {
   float qscale;     // softmax scale * log2(e)
   void* out;        // [B][H][M][128]
   void* kh;         // workspace: [B][H][nk][128] rebuilt keys
-  void* vt;         // workspace: [B][H][nk/64][128][64] rebuilt values, feature-major pages
+  void* vt;         // workspace: [B][H][nk/32][128][32] rebuilt values, feature-major blocks
 };
 size_t prefill_2d_ws_bytes(int B, int H, int n_keys);  // both rebuilt tensors
 hipError_t launch_prefill_2d(const Prefill2dArgs& a, hipStream_t stream);

@@ -29,8 +29,8 @@
 // Workspace layouts, chosen so that every MFMA operand of the attention is one
 // 16-byte LDS read:
 //   kh [B][H][nk][128]            keys token-major (a key's 128 features contiguous)
-//   vt [B][H][nk/64][128][64]     values feature-major per 64-key page; inside each
-//                                 16-key block the keys are stored in the order
+//   vt [B][H][nk/32][128][32]     values feature-major per 32-key block; inside each
+//                                 16-key run the keys are stored in the order
 //                                 0-3, 8-11, 4-7, 12-15 (the order in which a
 //                                 32x32 accumulator hands its rows to a lane half)
 // with nk = p0 + M rounded up to a page; tokens n >= p0 + M are written as 0.
@@ -49,6 +49,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kD = 128;            // d_head of both kernels
 constexpr int kThreads = 256;      // 4 wavefronts
+constexpr int kVBlk = 32;          // keys per block of the rebuilt values
 constexpr int kRTok = 128;         // tokens per rebuild workgroup (two pages)
 constexpr int kQBlock = 256;       // queries per attention workgroup (32 per wavefront)
 constexpr int kFThreads = 512;     // attention workgroup: 8 wavefronts
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kThreads) void recon2d_kernel(Prefill2dArgs a) {
         // permuted positions 16 blk + 8 g .. + 7 of the tile's 32
         const int tok0 = n0 + 32 * nt;
         uint16_t* dst = static_cast<uint16_t*>(a.vt) +
-                      ((bh * (a.nk / kPage) + tok0 / kPage) * kD + 32 * wave + col) * kPage + tok0 % kPage + 8 * g;
+                      ((bh * (a.nk / kVBlk) + tok0 / kVBlk) * kD + 32 * wave + col) * kVBlk + 8 * g;
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
           const f32x16& x = acc[nt];
@@ -335,7 +336,7 @@ void recon_ph_kernel(Prefill2dArgs a, int ppw) {
         // lane (feature col, half g), registers 8 blk .. + 7: tokens at permuted
         // positions 16 blk + 8 g .. + 7 of the tile
         uint16_t* dst = static_cast<uint16_t*>(a.vt) +
-                        (((size_t)bh * (a.nk / kPage) + pg) * kD + 32 * wave + col) * kPage + 32 * nt + 8 * g;
+                        (((size_t)bh * (a.nk / kVBlk) + 2 * pg + nt) * kD + 32 * wave + col) * kVBlk + 8 * g;
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk) {
           const f32x16& x = acc[nt];
@@ -403,7 +404,9 @@ void flash2d_kernel(Prefill2dArgs a) {
     for (int c = 0; c < CH; ++c) {
       const int ch = tid + c * kFThreads;
       *reinterpret_cast<uint4*>(&s_k[buf * KTILE + (ch >> 4) * KST + 8 * (ch & 15)]) = stk[set][c];
-      *reinterpret_cast<uint4*>(&s_v[buf * VTILE + (ch >> 3) * VST + 8 * (ch & 7)]) = stv[set][c];
+      // value chunk ch: block ch / 512, feature (ch / 4) % 128, keys 8 (ch % 4) .. + 7 of the block
+      *reinterpret_cast<uint4*>(&s_v[buf * VTILE + ((ch >> 2) & (kD - 1)) * VST + kVBlk * (ch >> 9) + 8 * (ch & 3)]) =
+          stv[set][c];
     }
   };
 
@@ -574,6 +577,428 @@ void flash2d_kernel(Prefill2dArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Attention for calls with few query blocks (a chunk appended to a longer
+// context).  One workgroup = 32 queries of one (b, h); its 8 wavefronts split
+// the keys instead of the queries: wavefront w takes the 32-key blocks w, w + 8,
+// ... and their (m, l, O) are combined through LDS at the end, so a call has
+// eight times the workgroups of flash2d_kernel.  No key block is shared between
+// wavefronts: each stages its own (8 KB of keys, 8 KB of values, whole lines;
+// operands loaded straight from memory touch 32 bytes of every row and ran 4 us
+// per block) in its own LDS, with the next block in flight in registers, so the
+// key loop has no barrier.  Products and the fp16 running max are
+// flash2d_kernel's.
+// ---------------------------------------------------------------------------
+constexpr int kSQ = 32;  // queries per workgroup
+constexpr int kSK = 32;  // keys per block
+static_assert(kSK == kVBlk, "a block of values is contiguous");
+__global__ __launch_bounds__(kFThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void flash2d_split_kernel(Prefill2dArgs a) {
+  constexpr int KS = kD / 16;
+  constexpr int NW = kFThreads / kWave;
+  constexpr int BLK = kSK * kD;         // elements of a staged block and axis
+  constexpr int CH = BLK / 8 / kWave;   // 16-byte chunks per lane and axis (8)
+  // each wavefront's key and value block, then its accumulators [register][lane]
+  __shared__ __attribute__((aligned(16))) uint16_t s_kv[NW][2 * BLK];
+  __shared__ float s_m[NW][kSQ], s_l[NW][kSQ];
+  static_assert(2 * BLK * sizeof(uint16_t) == kD / 2 * kWave * sizeof(float), "");
+
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int col = lane & 31, g = lane >> 5;
+  const int bh = blockIdx.x, h = bh % a.H;
+  const int M = a.M, p0 = a.p0;
+  const int nqb = (M + kSQ - 1) / kSQ;
+  const int q0 = (nqb - 1 - (int)blockIdx.y) * kSQ;  // heaviest (latest) query blocks first
+  const int myq = q0 + col;
+  const bool q_ok = myq < M;
+  const int kmax = p0 + min(q0 + kSQ, M);  // keys [0, kmax) matter to the workgroup
+  const int nblk = (kmax + kSK - 1) / kSK;
+
+  // Block j (keys 32 j .. + 31) is 8 KB contiguous per axis.  In LDS the 16-byte
+  // chunks of key row r (16 of them) are XORed with r % 16 and those of value
+  // row f (4) with (f / 4) % 4: 16-byte reads of 16 rows hit distinct banks.
+  const uint16_t* kbase = static_cast<const uint16_t*>(a.kh) + (size_t)bh * a.nk * kD + 8 * lane;
+  const uint16_t* vbase = static_cast<const uint16_t*>(a.vt) + (size_t)bh * a.nk * kD + 8 * lane;
+  uint16_t* const sk = s_kv[wave];
+  uint16_t* const sv = s_kv[wave] + BLK;
+  uint4 pk[CH], pv[CH];
+  auto load = [&](int j) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      pk[c] = ld16(kbase + (size_t)j * BLK + c * 8 * kWave);
+      pv[c] = ld16(vbase + (size_t)j * BLK + c * 8 * kWave);
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int kr = 4 * c + (lane >> 4), vr = 16 * c + (lane >> 2);
+      *reinterpret_cast<uint4*>(sk + kr * kD + (((lane & 15) ^ (kr & 15)) << 3)) = pk[c];
+      *reinterpret_cast<uint4*>(sv + vr * kVBlk + (((lane & 3) ^ ((vr >> 2) & 3)) << 3)) = pv[c];
+    }
+  };
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  if (wave < nblk) load(wave);
+
+  const float qs = a.qscale;
+  f16x8 qop[KS];
+  {
+    const bf16_t* qrow = static_cast<const bf16_t*>(a.q) + ((size_t)bh * M + (q_ok ? myq : 0)) * kD + 8 * g;
+    uint4 raw[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) raw[s] = ld16(qrow + 16 * s);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      float x[8];
+      Elem<bf16_t>::unpack(raw[s], x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qop[s][e] = (_Float16)(x[e] * qs);
+    }
+  }
+  const f16x8 a_one = {(_Float16)(g == 0 ? 1.f : 0.f), 0, 0, 0, 0, 0, 0, 0};
+
+  f32x16 oacc[kD / 32];
+#pragma unroll
+  for (int t = 0; t < kD / 32; ++t) oacc[t] = f32x16{0.f};
+  // seen: this lane's query has attended a key of this wavefront's blocks (a
+  // diagonal block may hold none); m is raised at the first one
+  float m_run = 0.f, l_lane = 0.f;
+  bool seen = false;
+  const int qpos = p0 + myq;
+  for (int j = wave; j < nblk; j += NW) {
+    store();
+    wave_sync();
+    if (j + NW < nblk) load(j + NW);
+    uint4 kop[KS], vop[kD / 32][2];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+      kop[s] = *reinterpret_cast<const uint4*>(sk + col * kD + (((2 * s + g) ^ (col & 15)) << 3));
+    const f16x8 b_m = {(_Float16)(g == 0 ? -m_run : 0.f), 0, 0, 0, 0, 0, 0, 0};
+    f32x16 sc = mfma_h(a_one, b_m, f32x16{0.f});
+#pragma unroll
+    for (int s = 0; s < KS; ++s) sc = mfma_h(as_f16x8(kop[s]), qop[s], sc);
+#pragma unroll
+    for (int t = 0; t < kD / 32; ++t)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        vop[t][u] = *reinterpret_cast<const uint4*>(sv + (32 * t + col) * kVBlk + (((2 * u + g) ^ ((col >> 2) & 3)) << 3));
+    __builtin_amdgcn_sched_barrier(0);
+    const int key0 = j * kSK;
+    if (__builtin_expect(key0 + kSK - 1 > p0 + q0, 0)) {
+      // key 8(r/4) + 4g + r%4 of the block is visible iff 8(r/4) + r%4 <= lim
+      const int lim = qpos - key0 - 4 * g;
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (8 * (r / 4) + (r % 4) > lim) sc[r] = neg_inf();
+    }
+    float m0 = fmaxf(fmaxf(sc[0], sc[1]), sc[2]), m1 = fmaxf(fmaxf(sc[8], sc[9]), sc[10]);
+#pragma unroll
+    for (int r = 3; r < 7; r += 2) {
+      m0 = fmaxf(fmaxf(m0, sc[r]), sc[r + 1]);
+      m1 = fmaxf(fmaxf(m1, sc[8 + r]), sc[9 + r]);
+    }
+    const float mx = half_swap_max(fmaxf(fmaxf(m0, sc[7]), fmaxf(m1, sc[15])));
+    const bool raise = mx > kLazy || (!seen && mx > neg_inf());
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
+      if (raise) {
+        const float m_new = (float)(_Float16)(m_run + mx);
+        const float delta = m_new - m_run;  // exact: both are fp16 values
+        const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 0.f;
+#pragma unroll
+        for (int t = 0; t < kD / 32; ++t) oacc[t] *= alpha;
+        l_lane *= alpha;
+        sc -= delta;
+        m_run = m_new;
+        seen = true;
+      }
+    }
+    f16x8 pop[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pop[u][e] = (_Float16)__builtin_amdgcn_exp2f(sc[8 * u + e]);
+    const f16x2 ones = {(_Float16)1.0f, (_Float16)1.0f};
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; e += 2)
+        l_lane = __builtin_amdgcn_fdot2(f16x2{pop[u][e], pop[u][e + 1]}, ones, l_lane, false);
+#pragma unroll
+    for (int t = 0; t < kD / 32; ++t)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) oacc[t] = mfma_h(as_f16x8(vop[t][u]), pop[u], oacc[t]);
+    wave_sync();  // the block's LDS reads are done before the next one is stored
+  }
+
+  // ---- combine the wavefronts: wavefront w finishes registers 8 w .. 8 w + 7 ----
+  float* const s_o = reinterpret_cast<float*>(s_kv);  // [wave][register][lane]
+#pragma unroll
+  for (int t = 0; t < kD / 32; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s_o[(wave * (kD / 2) + 16 * t + r) * kWave + lane] = oacc[t][r];
+  l_lane = half_swap_sum(l_lane);
+  if (g == 0) {
+    s_m[wave][col] = seen ? m_run : neg_inf();
+    s_l[wave][col] = l_lane;
+  }
+  __syncthreads();
+  float mm = neg_inf(), l = 0.f, wt[NW];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) mm = fmaxf(mm, s_m[w][col]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    wt[w] = __builtin_amdgcn_exp2f(s_m[w][col] - mm);  // 0 for a wavefront that saw no key
+    l = fmaf(wt[w], s_l[w][col], l);
+  }
+  if (!q_ok) return;
+  const float inv_l = 1.0f / l;
+  const bf16_t* muv = a.muv ? static_cast<const bf16_t*>(a.muv) + (size_t)h * kD : nullptr;
+  const size_t orow = ((size_t)bh * M + myq) * kD;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int r0 = 8 * wave + 4 * c;  // tile r0 / 16, registers r0 % 16 ..: 4 consecutive features
+    const int i0 = 32 * (wave >> 1) + 8 * ((r0 & 15) >> 2) + 4 * g;
+    float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = fmaf(wt[w], s_o[(w * (kD / 2) + r0 + e) * kWave + lane], o[e]);
+    const uint2 mw = muv ? *reinterpret_cast<const uint2*>(muv + i0) : make_uint2(0, 0);
+    const float v0 = fmaf(o[0], inv_l, bf16_lo(mw.x)), v1 = fmaf(o[1], inv_l, bf16_hi(mw.x));
+    const float v2 = fmaf(o[2], inv_l, bf16_lo(mw.y)), v3 = fmaf(o[3], inv_l, bf16_hi(mw.y));
+    if (a.out_dtype == LLA_F32)
+      *reinterpret_cast<float4*>(static_cast<float*>(a.out) + orow + i0) = make_float4(v0, v1, v2, v3);
+    else
+      *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.out) + orow + i0) = make_uint2(pack2(v0, v1), pack2(v2, v3));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Attention between the two: 8 / S query groups of 32 by S key streams in a
+// workgroup.  128 keys per round are staged for all (K rows and V blocks as
+// in flash2d_split_kernel's swizzled layout, double buffered, the next
+// round's loads in flight in registers); stream s takes keys 128 / S * s .. of
+// every round, and the streams' (m, l, O) are combined through LDS at the end.
+// ---------------------------------------------------------------------------
+template <int S>
+__global__ __launch_bounds__(kFThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void flash2d_streams_kernel(Prefill2dArgs a) {
+  constexpr int KS = kD / 16;
+  constexpr int NW = kFThreads / kWave, QW = NW / S;
+  constexpr int RK = 128;                       // keys per round
+  constexpr int NT = RK / S / 32;               // 32-key tiles of a stream's share
+  constexpr int QB = 32 * QW;                   // queries per workgroup
+  constexpr int CH = RK * kD / 8 / kFThreads;   // 16-byte chunks per thread and axis (4)
+  constexpr int BUF = 2 * RK * kD;              // elements of one buffer: keys, then values
+  __shared__ __attribute__((aligned(16))) uint16_t s_kv[2 * BUF];
+  __shared__ float s_m[NW][32], s_l[NW][32];
+  static_assert(2 * BUF * sizeof(uint16_t) == NW * kD / 2 * kWave * sizeof(float), "");
+
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int st = wave % S, qg = wave / S;
+  const int col = lane & 31, g = lane >> 5;
+  const int bh = blockIdx.x, h = bh % a.H;
+  const int M = a.M, p0 = a.p0;
+  const int nqb = (M + QB - 1) / QB;
+  const int q0 = (nqb - 1 - (int)blockIdx.y) * QB;  // heaviest (latest) query blocks first
+  const int qw0 = q0 + 32 * qg, myq = qw0 + col;
+  const bool q_ok = myq < M, wave_live = qw0 < M;
+  const int qlast_w = min(qw0 + 31, M - 1);
+  const int kmax = p0 + min(q0 + QB, M);  // keys [0, kmax) matter to the workgroup
+  const int rounds = (kmax + RK - 1) / RK;
+
+  // staging: chunk ch = tid + 512 c: key row ch / 16, or value block ch / 512 and
+  // feature (ch / 4) % 128.  The last round may reach past the rebuilt keys: it
+  // re-reads the last row or block (masked, like every key past a query).
+  const uint16_t* kbase = static_cast<const uint16_t*>(a.kh) + (size_t)bh * a.nk * kD;
+  const uint16_t* vbase = static_cast<const uint16_t*>(a.vt) + (size_t)bh * a.nk * kD;
+  uint4 pk[CH], pv[CH];
+  auto load = [&](int i) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int kr = min(RK * i + 32 * c + (tid >> 4), a.nk - 1);
+      const int vb = min(RK / kVBlk * i + c, a.nk / kVBlk - 1);
+      pk[c] = ld16(kbase + (size_t)kr * kD + 8 * (tid & 15));
+      pv[c] = ld16(vbase + (size_t)vb * kVBlk * kD + 8 * tid);
+    }
+  };
+  const int kst = (tid >> 4) * kD + (((tid & 15) ^ ((tid >> 4) & 15)) << 3);
+  const int vst = (tid >> 2) * kVBlk + (((tid & 3) ^ ((tid >> 4) & 3)) << 3);
+  auto store = [&](int buf) {
+    uint16_t* d = s_kv + buf * BUF;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      *reinterpret_cast<uint4*>(d + 32 * c * kD + kst) = pk[c];
+      *reinterpret_cast<uint4*>(d + RK * kD + c * kVBlk * kD + vst) = pv[c];
+    }
+  };
+  load(0);
+
+  const float qs = a.qscale;
+  f16x8 qop[KS];
+  {
+    const bf16_t* qrow = static_cast<const bf16_t*>(a.q) + ((size_t)bh * M + (q_ok ? myq : 0)) * kD + 8 * g;
+    uint4 raw[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) raw[s] = ld16(qrow + 16 * s);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      float x[8];
+      Elem<bf16_t>::unpack(raw[s], x);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qop[s][e] = (_Float16)(x[e] * qs);
+    }
+  }
+  const f16x8 a_one = {(_Float16)(g == 0 ? 1.f : 0.f), 0, 0, 0, 0, 0, 0, 0};
+
+  f32x16 oacc[kD / 32];
+#pragma unroll
+  for (int t = 0; t < kD / 32; ++t) oacc[t] = f32x16{0.f};
+  float m_run = 0.f, l_lane = 0.f;
+  bool seen = false;
+  const int qpos = p0 + myq;
+  store(0);
+  load(min(1, rounds - 1));
+  __syncthreads();
+  for (int i = 0; i < rounds; ++i) {
+    const int buf = i & 1;
+    if (i + 1 < rounds) store(buf ^ 1);
+    if (i + 2 < rounds) load(i + 2);
+    const int key0 = RK * i + 32 * NT * st;
+    if (wave_live && key0 <= p0 + qlast_w) {
+      const uint16_t* sk = s_kv + buf * BUF + (32 * NT * st + col) * kD;
+      const uint16_t* sv = s_kv + buf * BUF + RK * kD + NT * st * kVBlk * kD + col * kVBlk;
+      uint4 kop[KS][NT];
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt)
+          kop[s][kt] = *reinterpret_cast<const uint4*>(sk + 32 * kt * kD + (((2 * s + g) ^ (col & 15)) << 3));
+      __builtin_amdgcn_sched_barrier(0);
+      const f16x8 b_m = {(_Float16)(g == 0 ? -m_run : 0.f), 0, 0, 0, 0, 0, 0, 0};
+      f32x16 sc[NT];
+#pragma unroll
+      for (int kt = 0; kt < NT; ++kt) sc[kt] = mfma_h(a_one, b_m, f32x16{0.f});
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt) sc[kt] = mfma_h(as_f16x8(kop[s][kt]), qop[s], sc[kt]);
+      uint4 vop[NT][kD / 32][2];
+#pragma unroll
+      for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+        for (int t = 0; t < kD / 32; ++t)
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+            vop[kt][t][u] = *reinterpret_cast<const uint4*>(sv + (kt * kD + 32 * t) * kVBlk + (((2 * u + g) ^ ((col >> 2) & 3)) << 3));
+      __builtin_amdgcn_sched_barrier(0);
+      if (__builtin_expect(key0 + 32 * NT - 1 > p0 + qw0, 0)) {
+        const int lim = qpos - key0 - 4 * g;
+#pragma unroll
+        for (int kt = 0; kt < NT; ++kt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (32 * kt + 8 * (r / 4) + (r % 4) > lim) sc[kt][r] = neg_inf();
+      }
+      float mx = neg_inf();
+#pragma unroll
+      for (int kt = 0; kt < NT; ++kt) {
+        float m0 = fmaxf(fmaxf(sc[kt][0], sc[kt][1]), sc[kt][2]), m1 = fmaxf(fmaxf(sc[kt][8], sc[kt][9]), sc[kt][10]);
+#pragma unroll
+        for (int r = 3; r < 7; r += 2) {
+          m0 = fmaxf(fmaxf(m0, sc[kt][r]), sc[kt][r + 1]);
+          m1 = fmaxf(fmaxf(m1, sc[kt][8 + r]), sc[kt][9 + r]);
+        }
+        mx = fmaxf(mx, fmaxf(fmaxf(m0, sc[kt][7]), fmaxf(m1, sc[kt][15])));
+      }
+      mx = half_swap_max(mx);
+      const bool raise = mx > kLazy || (!seen && mx > neg_inf());
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
+        if (raise) {
+          const float m_new = (float)(_Float16)(m_run + mx);
+          const float delta = m_new - m_run;  // exact: both are fp16 values
+          const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 0.f;
+#pragma unroll
+          for (int t = 0; t < kD / 32; ++t) oacc[t] *= alpha;
+          l_lane *= alpha;
+#pragma unroll
+          for (int kt = 0; kt < NT; ++kt) sc[kt] -= delta;
+          m_run = m_new;
+          seen = true;
+        }
+      }
+#pragma unroll
+      for (int kt = 0; kt < NT; ++kt) {
+        f16x8 pop[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) pop[u][e] = (_Float16)__builtin_amdgcn_exp2f(sc[kt][8 * u + e]);
+        const f16x2 ones = {(_Float16)1.0f, (_Float16)1.0f};
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int e = 0; e < 8; e += 2)
+            l_lane = __builtin_amdgcn_fdot2(f16x2{pop[u][e], pop[u][e + 1]}, ones, l_lane, false);
+#pragma unroll
+        for (int t = 0; t < kD / 32; ++t)
+#pragma unroll
+          for (int u = 0; u < 2; ++u) oacc[t] = mfma_h(as_f16x8(vop[kt][t][u]), pop[u], oacc[t]);
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- combine the streams: wavefront (qg, st) finishes registers 64 / S st .. of its queries ----
+  constexpr int RPW = kD / 2 / S;
+  float* const s_o = reinterpret_cast<float*>(s_kv);  // [wave][register][lane]
+#pragma unroll
+  for (int t = 0; t < kD / 32; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s_o[(wave * (kD / 2) + 16 * t + r) * kWave + lane] = oacc[t][r];
+  l_lane = half_swap_sum(l_lane);
+  if (g == 0) {
+    s_m[wave][col] = seen ? m_run : neg_inf();
+    s_l[wave][col] = l_lane;
+  }
+  __syncthreads();
+  float mm = neg_inf(), l = 0.f, wt[S];
+#pragma unroll
+  for (int w = 0; w < S; ++w) mm = fmaxf(mm, s_m[qg * S + w][col]);
+#pragma unroll
+  for (int w = 0; w < S; ++w) {
+    wt[w] = __builtin_amdgcn_exp2f(s_m[qg * S + w][col] - mm);  // 0 for a stream that saw no key
+    l = fmaf(wt[w], s_l[qg * S + w][col], l);
+  }
+  if (!q_ok) return;
+  const float inv_l = 1.0f / l;
+  const bf16_t* muv = a.muv ? static_cast<const bf16_t*>(a.muv) + (size_t)h * kD : nullptr;
+  const size_t orow = ((size_t)bh * M + myq) * kD;
+#pragma unroll
+  for (int c = 0; c < RPW / 4; ++c) {
+    const int r0 = RPW * st + 4 * c;  // tile r0 / 16, registers r0 % 16 ..: 4 consecutive features
+    const int i0 = 32 * (r0 >> 4) + 8 * ((r0 & 15) >> 2) + 4 * g;
+    float o[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < S; ++w)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = fmaf(wt[w], s_o[((qg * S + w) * (kD / 2) + r0 + e) * kWave + lane], o[e]);
+    const uint2 mw = muv ? *reinterpret_cast<const uint2*>(muv + i0) : make_uint2(0, 0);
+    const float v0 = fmaf(o[0], inv_l, bf16_lo(mw.x)), v1 = fmaf(o[1], inv_l, bf16_hi(mw.x));
+    const float v2 = fmaf(o[2], inv_l, bf16_lo(mw.y)), v3 = fmaf(o[3], inv_l, bf16_hi(mw.y));
+    if (a.out_dtype == LLA_F32)
+      *reinterpret_cast<float4*>(static_cast<float*>(a.out) + orow + i0) = make_float4(v0, v1, v2, v3);
+    else
+      *reinterpret_cast<uint2*>(static_cast<bf16_t*>(a.out) + orow + i0) = make_uint2(pack2(v0, v1), pack2(v2, v3));
+  }
+}
+
 template <int AXIS, int KS>
 hipError_t launch_recon(const Prefill2dArgs& a, hipStream_t stream) {
   const dim3 grid((a.nk + kRTok - 1) / kRTok, a.B);
@@ -595,6 +1020,51 @@ hipError_t launch_recon_r(const Prefill2dArgs& a, int r, hipStream_t stream) {
   }
 }
 
+// Key streams per workgroup of the attention: 1 (flash2d_kernel, 256 queries),
+// 2, 4 (flash2d_streams_kernel, 128 and 64 queries) or 8 (flash2d_split_kernel,
+// 32).  Fewer queries per workgroup put more workgroups on the machine, each
+// with a shorter key loop, but stage every key for fewer queries: at a full
+// machine (4 x 4096 tokens, 16 heads) they run at 1, 0.85, 0.66 and 0.52 of
+// flash2d_kernel's rate.  The estimate adds, for one compute unit, the keys of
+// the heaviest workgroup of every round of the machine (workgroups start
+// heaviest first) and a fixed cost per workgroup, in keys of flash2d_kernel's
+// loop.  Attention and rebuilds per call at (96, 160), 16 heads, 1 / 2 / 4 / 8
+// streams: 300 tokens after 7000 211 / 150 / 118 / 85 us; 1024 tokens 47 / 38 /
+// 32 / 33; 2048 tokens 76 / 60 / 55 / 64; 4096 tokens 134 / 114 / 139 / 163;
+// 4 x 300 after 2000 104 / 87 / 97 / 101; 4 x 2048 138 / 160 / 191 / 242.
+int key_streams(const Prefill2dArgs& a) {
+  const int cus = device_cu_count();
+  const double rate[4] = {1.0, 2 * 0.85, 4 * 0.66, 8 * 0.52}, fixed[4] = {40, 100, 150, 240};
+  int best = 1;
+  double best_t = 0.0;
+  for (int k = 0; k < 4; ++k) {
+    const int qb = kQBlock >> k, nqb = (a.M + qb - 1) / qb;
+    const long wgs = (long)a.B * a.H * nqb;
+    if (k == 0 && wgs > 8L * cus) return 1;
+    if (nqb > 65535) break;
+    double t = 0.0;
+    for (long r = 0; r < wgs; r += cus)
+      t += a.p0 + min((nqb - r / ((long)a.B * a.H)) * qb, (long)a.M) + fixed[k];
+    t /= rate[k];
+    if (k == 0 || t < 0.97 * best_t) {
+      best = 1 << k;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_attention(const Prefill2dArgs& a, hipStream_t stream) {
+  const int bh = a.B * a.H, threads = kFThreads;
+  switch (key_streams(a)) {
+    case 1: hipLaunchKernelGGL(flash2d_kernel, dim3(bh, (a.M + 255) / 256), dim3(threads), 0, stream, a); break;
+    case 2: hipLaunchKernelGGL(flash2d_streams_kernel<2>, dim3(bh, (a.M + 127) / 128), dim3(threads), 0, stream, a); break;
+    case 4: hipLaunchKernelGGL(flash2d_streams_kernel<4>, dim3(bh, (a.M + 63) / 64), dim3(threads), 0, stream, a); break;
+    default: hipLaunchKernelGGL(flash2d_split_kernel, dim3(bh, (a.M + 31) / 32), dim3(threads), 0, stream, a); break;
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
 
 size_t prefill_2d_ws_bytes(int B, int H, int n_keys) {
@@ -607,9 +1077,7 @@ hipError_t launch_prefill_2d(const Prefill2dArgs& a, hipStream_t stream) {
   if (e != hipSuccess) return e;
   e = launch_recon_r<1>(a, a.rv, stream);
   if (e != hipSuccess) return e;
-  const dim3 grid(a.B * a.H, (a.M + kQBlock - 1) / kQBlock);
-  hipLaunchKernelGGL(flash2d_kernel, grid, dim3(kFThreads), 0, stream, a);
-  return hipGetLastError();
+  return launch_attention(a, stream);
 }
 
 template <int AXIS>
@@ -638,9 +1106,7 @@ hipError_t launch_prefill_rebuild(const Prefill2dArgs& a, hipStream_t stream) {
   if (e != hipSuccess) return e;
   e = launch_recon_ph<1>(a, a.rv, stream);
   if (e != hipSuccess) return e;
-  const dim3 grid(a.B * a.H, (a.M + kQBlock - 1) / kQBlock);
-  hipLaunchKernelGGL(flash2d_kernel, grid, dim3(kFThreads), 0, stream, a);
-  return hipGetLastError();
+  return launch_attention(a, stream);
 }
 
 }  // namespace lla

@@ -205,6 +205,37 @@ def test_bf16_prefill_tier_peaked_and_rising(qmul, kramp):
                  f"q x{qmul} ramp {kramp}")
 
 
+@pytest.mark.parametrize("B,M,p0", [(1, 33, 70), (1, 300, 2000),      # 8 key streams on a 256-CU device
+                                    (1, 1000, 31),                     # 4
+                                    (4, 270, 1500), (1, 3970, 5),      # 2
+                                    (4, 1900, 0)])                     # 1
+# The queries and rebuilt keys enter in fp16 (relative error 2^-12 each), so a base-2 logit L carries an error
+# of up to |L| 2^-11: a weight is off by |L| 2^-11 ln 2.  With the ramp L reaches about 45 (a standard deviation
+# of 10), 1.5%; queries x 4 on top of it would make that 6%, of values near 28, above the 2e-2 bar by the
+# rounding of the operands alone.
+@pytest.mark.parametrize("qmul,kramp,means", [(1.0, 0.0, True), (1.0, 6.0, False)])
+def test_bf16_prefill_key_streams(B, M, p0, qmul, kramp, means):
+    """Every split of the attention's workgroups between queries and keys, at the
+    edges of their query groups, key tiles and rounds; latents growing along the
+    context raise the running maximum in every stream."""
+    wl = W.Workload("pf_streams", 1, 16, 128, 4, B, 0, ((96, 160),), torch.bfloat16)
+    log(f"key streams B={B} M={M} p0={p0} q x{qmul} ramp {kramp}")
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, 96, 160, B, M, p0, torch.bfloat16, means=means, qmul=qmul,
+                                                kramp=kramp)
+    out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(out).all())
+    edges = {e + d for e in (0, 32, 64, 128, 256, M - M % 32, M - M % 256, M - 1) for d in (-1, 0, 1)}
+    rows = sorted(r for r in edges if 0 <= r < M)
+    heads = [0, 7, 15]
+    o = f64(out[:, heads][:, :, rows])
+    muk, muv = (None if t is None else t[heads] for t in (muk, muv))
+    ref = np.stack([_rows_absorbed(q[:, [h]], ck[:, [h]], cv[:, [h]], uk[[h]], uv[[h]],
+                                   None if muk is None else muk[[i]], None if muv is None else muv[[i]], p0,
+                                   rows=rows)[:, 0] for i, h in enumerate(heads)], axis=1)
+    assert_close(o, ref, torch.bfloat16, "key streams")
+
+
 @pytest.mark.slow
 @pytest.mark.parametrize("r_k,r_v", [(96, 160), (288, 480)])
 def test_full_prefill_tier(r_k, r_v):
