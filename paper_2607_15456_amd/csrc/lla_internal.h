@@ -116,6 +116,7 @@ struct Prefill2dArgs {
   const void* muv;  // [H][128] or null
   float qscale;     // softmax scale * log2(e)
   void* out;        // [B][H][M][128]
+  int hpw;          // heads per workgroup of the LLA-2D rebuild
   void* kh;         // workspace: [B][H][nk][128] rebuilt keys
   void* vt;         // workspace: [B][H][nk/32][128][32] rebuilt values, feature-major blocks
 };

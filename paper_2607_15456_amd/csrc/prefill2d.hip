@@ -91,8 +91,8 @@ __device__ __forceinline__ float half_swap_sum(float x) {
 }
 
 // ---------------------------------------------------------------------------
-// Rebuild.  One workgroup = 128 tokens of one sequence, every head: the latent
-// tile is staged once in LDS token-major (a token's r features contiguous) and
+// Rebuild.  One workgroup = 128 tokens of one sequence and a run of heads (all of
+// them for a long prompt): the latent tile is staged once in LDS token-major (a token's r features contiguous) and
 // wavefront w computes features 32w .. 32w + 31 of every head, with that
 // head's up-projection rows as the other operand (16-byte loads).
 //   keys:   D = K^T (M = feature, N = token, K = latent feature j), so a lane
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kThreads) void recon2d_kernel(Prefill2dArgs a) {
   };
   // every operand load of a head is issued before its first product, so the
   // products of the early K-steps overlap the later loads
-  for (int h = 0; h < H; ++h) {
+  for (int h = blockIdx.z * a.hpw; h < min(H, (int)(blockIdx.z + 1) * a.hpw); ++h) {
     load_u(h, ua);
     switch (ntile) {  // uniform; 2 or 4 (the key count is a multiple of 64)
       case 4: head(h, ua, IntC<4>{}); break;
@@ -1000,8 +1000,16 @@ void flash2d_streams_kernel(Prefill2dArgs a) {
 }
 
 template <int AXIS, int KS>
-hipError_t launch_recon(const Prefill2dArgs& a, hipStream_t stream) {
-  const dim3 grid((a.nk + kRTok - 1) / kRTok, a.B);
+hipError_t launch_recon(const Prefill2dArgs& args, hipStream_t stream) {
+  Prefill2dArgs a = args;
+  // heads per workgroup: with fewer token blocks than compute units the heads are
+  // split too, up to one workgroup per unit (a value tile fills a unit's LDS);
+  // both axes and the attention per call at (288, 480), one against this many
+  // groups: 300 tokens 115 -> 31 us, 1024 tokens 140 -> 47, 2 x 4096 256 -> 203
+  const int nb = (a.nk + kRTok - 1) / kRTok;
+  const long groups = max(1L, (long)device_cu_count() / ((long)nb * a.B));
+  a.hpw = (int)((a.H + groups - 1) / groups);
+  const dim3 grid(nb, a.B, (a.H + a.hpw - 1) / a.hpw);
   hipLaunchKernelGGL((recon2d_kernel<AXIS, KS>), grid, dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }

@@ -110,6 +110,16 @@ def test_prefill_2d_edges(B, H, M, p0, n_max):
     assert_close(got, ref, torch.bfloat16, f"edges B={B} H={H} M={M} p0={p0}")
 
 
+@pytest.mark.parametrize("B,H", [(50, 3), (50, 5), (130, 2)])
+def test_prefill_2d_head_groups(B, H):
+    """Rebuilds whose token blocks (100 of 128 tokens, 260) leave room for two head
+    groups per block, the last one shorter, or for none, on a 256-CU device."""
+    log(f"prefill 2d head groups B={B} H={H}")
+    got, h = _run(B, H, 130, 3, 32, 16, seed=6, mu=True)
+    ref = oracle.prefill_attn_2d_batched(h["q"], h["ck"], h["cv"], h["uk"], h["uv"], h["muk"], h["muv"], p0=3)
+    assert_close(got, ref, torch.bfloat16, f"head groups B={B} H={H}")
+
+
 def test_prefill_2d_rejects_small_workspace():
     B, H, M = 1, 2, 70
     wl = _wl(H)
