@@ -13,7 +13,7 @@
 // The pass reads x once (HBM-bound at the paper's ranks: about (r_k + r_v)/2
 // flop per byte).
 //
-// fp32: a plain LDS-tiled VALU GEMM with the same output mapping.
+// fp32: the same product on the fp32 matrix instructions, 32 x 32 tiles.
 
 #include "lla_device.h"
 #include "lla_internal.h"
@@ -637,37 +637,77 @@ __global__ __launch_bounds__(256) void encode_reduce_kernel(EncodeArgs a, int nr
   }
 }
 
-// fp32: 16 tokens x 16 rows per workgroup, K staged through LDS in chunks of 64.
-constexpr int kT = 16, kKC = 64;
-__global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a) {
-  __shared__ float s_x[kT][kKC + 1];
-  __shared__ float s_w[kT][kKC + 1];
-  const int axis = blockIdx.z / a.H, h = blockIdx.z - axis * a.H;
-  const int r = pick(a.r, axis), K = a.K, TT = a.B * a.M;
-  if (blockIdx.y * kT >= r) return;
-  const int tt = threadIdx.x / kT, rr = threadIdx.x % kT;
-  const int tok = blockIdx.x * kT + tt, row = blockIdx.y * kT + rr;
-  const float* x = static_cast<const float*>(pick(a.x, axis));
-  const float* w = static_cast<const float*>(pick(a.wdt, axis)) + (size_t)h * r * K;
-  const float* mu = pick(a.mu, axis) ? static_cast<const float*>(pick(a.mu, axis)) + (size_t)h * K : nullptr;
-  float acc = 0.f;
-  for (int k0 = 0; k0 < K; k0 += kKC) {
-    for (int e = threadIdx.x; e < kT * kKC; e += 256) {
-      const int i = e / kKC, kk = e % kKC, k = k0 + kk;
-      const int t = blockIdx.x * kT + i, ro = blockIdx.y * kT + i;
-      float xv = 0.f;
-      if (t < TT && k < K) xv = x[((size_t)t * a.H + h) * K + k] - (mu ? mu[k] : 0.f);
-      s_x[i][kk] = xv;
-      s_w[i][kk] = (ro < r && k < K) ? w[(size_t)ro * K + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < kKC; ++kk) acc = fmaf(s_x[tt][kk], s_w[rr][kk], acc);
-    __syncthreads();
+// fp32, on the fp32 matrix instructions (v_mfma_f32_16x16x4_f32: products and
+// sums in fp32).  Workgroup = 32 rows x 32 tokens of one (axis, head); its four
+// wavefronts split K in turn, 16 values at a time, each with a 2 x 2 block of
+// 16x16 tiles: a lane's 16 bytes (row or token lane % 16, values 4 (lane / 16) ..)
+// are the operands of four products, straight from memory, so an operand is
+// loaded twice per product pair instead of once.  The four partial blocks add
+// through LDS in wavefront order, and a row of 32 tokens leaves as 128
+// consecutive bytes.  x - mu is formed in fp32 before the product.
+// grid: x = token block x row block (axis k, then v), y = head; a head's
+// workgroups on one XCD, whose L2 then holds its weights.  500 tokens of 16
+// heads, K = 512, (96, 160): 159 us with LDS-staged vector products (two LDS
+// reads per multiply-add), 37 us here (14 us of products at the matrix rate).
+constexpr int kFS = 36;  // LDS row stride of a partial block
+__global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a, int nrc_k, int nrc) {
+  __shared__ __attribute__((aligned(16))) float s_part[4][32 * kFS];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  int bx, h;
+  xcd_head_order(bx, h, true);
+  const int tb = (unsigned)bx / (unsigned)nrc, rc_ = bx - tb * nrc;
+  const int axis = rc_ >= nrc_k ? 1 : 0, rc = rc_ - axis * nrc_k;
+  const int r = pick(a.r, axis), K = a.K, H = a.H, TT = a.B * a.M;
+  const int c = lane & 15, g = lane >> 4;
+  const float* mu = pick(a.mu, axis) ? static_cast<const float*>(pick(a.mu, axis)) + (size_t)h * K + 4 * g : nullptr;
+  const float *xp[2], *wp[2];  // rows and tokens past the last one re-read it: never stored
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    xp[u] = static_cast<const float*>(pick(a.x, axis)) + ((size_t)min(tb * 32 + 16 * u + c, TT - 1) * H + h) * K + 4 * g;
+    wp[u] = static_cast<const float*>(pick(a.wdt, axis)) + ((size_t)h * r + min(rc * 32 + 16 * u + c, r - 1)) * K + 4 * g;
   }
-  if (tok < TT && row < r) {
-    const int b = tok / a.M, pos = ring_slot(a.pos0 + (tok - b * a.M), a.sink, a.window);
-    static_cast<float*>(pick(a.c, axis))[cache_index(b, h, a.H, a.n_max, r, pos, row, axis == 0 && a.k_token_major)] = acc;
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) acc[u][0] = acc[u][1] = f32x4{0.f};
+#pragma unroll 2
+  for (int k0 = 16 * wave; k0 < K; k0 += 64) {
+    f32x4 x[2], w[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      x[u] = *reinterpret_cast<const f32x4*>(xp[u] + k0);
+      w[u] = *reinterpret_cast<const f32x4*>(wp[u] + k0);
+    }
+    if (mu) {
+      const f32x4 m = *reinterpret_cast<const f32x4*>(mu + k0);
+      x[0] -= m;
+      x[1] -= m;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+          acc[u][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][e], x[v][e], acc[u][v], 0, 0, 0);
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s_part[wave][(16 * u + 4 * g + e) * kFS + 16 * v + c] = acc[u][v][e];
+  __syncthreads();
+  const int t = tb * 32 + (tid & 31);
+  if (t >= TT) return;
+  const int b = t / a.M, pos = ring_slot(a.pos0 + (t - b * a.M), a.sink, a.window);
+  float* out = static_cast<float*>(pick(a.c, axis));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int rl = (tid >> 5) + 8 * i, row = rc * 32 + rl;
+    const int e = rl * kFS + (tid & 31);
+    if (row < r)
+      out[cache_index(b, h, H, a.n_max, r, pos, row, axis == 0 && a.k_token_major)] =
+          s_part[0][e] + s_part[1][e] + s_part[2][e] + s_part[3][e];
   }
 }
 
@@ -742,8 +782,9 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
     dim3 grid(blocks, (a.H + heads_per_wg - 1) / heads_per_wg, 2 * nrc);
     hipLaunchKernelGGL(encode_bf16_kernel, grid, dim3(256), 0, stream, a, heads_per_wg, rt_per_wg, nrc);
   } else {
-    dim3 grid((TT + kT - 1) / kT, (rmax + kT - 1) / kT, 2 * a.H);
-    hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, a);
+    const int nrc_k = (a.r[0] + 31) / 32, nrc = nrc_k + (a.r[1] + 31) / 32;
+    dim3 grid((TT + 31) / 32 * nrc, a.H);
+    hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, a, nrc_k, nrc);
   }
   return hipGetLastError();
 }

@@ -209,3 +209,14 @@ def test_encode_gemm_ring_slots(r_k, r_v, means):
         ref = np.concatenate(refs, axis=2)[:, :, keep]          # [B, H, kept, r]
         got = f64(lla.from_paged(c))[:, :, slots]
         assert_close(got, ref, torch.bfloat16, f"ring GEMM write {name}")
+
+
+@pytest.mark.parametrize("r_k,r_v", [(1, 33), (31, 32), (96, 160)])
+@pytest.mark.parametrize("M,pos0,d_head", [(1, 63, 32), (11, 60, 96), (33, 5, 128)])
+def test_fp32_tiles(r_k, r_v, M, pos0, d_head):
+    """fp32 writes at the edges of their 32 x 32 tiles, K = 32 (two of the four
+    wavefronts idle), 96 and 512."""
+    wl = W.Workload("enc_f32", 1, 3, d_head, 4 if d_head == 128 else 1, 3, 0, ((18, 30),), torch.float32)
+    log(f"encode fp32 r=({r_k},{r_v}) M={M} pos0={pos0} d={d_head}")
+    inputs, ck, cv = _run(wl, r_k, r_v, 3, M, pos0, 192, True, torch.float32)
+    _check(wl, inputs, ck, cv, pos0, M, torch.float32, "fp32 tiles")
