@@ -40,8 +40,9 @@
 // up-projections with vector loads and reduce in a fixed order, so results
 // are bitwise reproducible.
 //
-// The same kernel serves the fp32 causal prefill: M queries per (b, h), query m
-// attending positions [0, p0 + m], one workgroup per query.
+// The same kernel serves fp32 causal prefills of few queries (M queries per
+// (b, h), query m attending positions [0, p0 + m], one workgroup per query)
+// where the fp32 matrix kernel is not the faster one.
 
 #include "lla_device.h"
 #include "lla_internal.h"
@@ -1063,6 +1064,7 @@ hipError_t dispatch(const DecodeArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
+  if (a.matrix) return a.dtype == LLA_F32 ? launch_attn_f32(a, stream) : hipErrorInvalidValue;
   if (a.dtype == LLA_BF16) return dispatch<bf16_t>(a, stream);
   return dispatch<float>(a, stream);
 }

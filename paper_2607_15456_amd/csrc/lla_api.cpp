@@ -75,6 +75,7 @@ size_t workspace_bytes(int B, int H, int r_v, int n_ctx) {
 // LLA_DECODE_SHORT_GROUPS override the choice (for tuning sweeps).
 struct DecodeShape {
   int waves, splits, deep, half, shortk;
+  int matrix = 0;  // fp32: the matrix kernel
 };
 
 int env_int(const char* name) {
@@ -90,7 +91,36 @@ int row_blocks_of(int r_k, int r_v, int d_rope) {
   return std::max((r_k + 7) / 8 + d_rope / 8, (r_v + 7) / 8);
 }
 
-DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int row_blocks) {
+// fp32 decode: the matrix kernel (one 8-wavefront workgroup per slice, each
+// wavefront on a page) or the scan.  Four calls over 16 heads, matrix against
+// scan: one sequence of 512 tokens (96, 160) 97 / 104 us, of 1500 at two
+// sequences 123 / 279, (192, 320) 2048 tokens 196 / 776; from 129 units the
+// scan's wavefronts already stream side by side ((96, 160) 16 x 1024 266 / 208)
+// except at r_v > 256, where its rows no longer fit the registers ((192, 320)
+// 64 x 2048 2986 / 3632).  At r_v <= 32 most of the matrix kernel's wavefronts
+// have no value tile (4 x 4096 118 / 90).  Contexts of 64 pages and more over
+// few units keep the scan and its split counts, which lla_decode_splits
+// reports.
+bool f32_matrix_decode(int units, int pages, int r_v) {
+  const int cus = lla::device_cu_count();
+  if (r_v > 256) return pages < 64 || units >= cus;
+  return r_v > 32 && pages < 64 && 2 * units <= cus;
+}
+
+// fp32 prefill: a 16-query tile of the matrix kernel costs about what the
+// scan's workgroups for 16 queries at r_v = 30 do, less at larger ranks or
+// more queries (four calls, one sequence of 16 heads, matrix / scan: 16
+// queries after 2000 tokens (18, 30) 117 / 96 us, (36, 60) 151 / 157, (96, 160)
+// 310 / 339; 64 queries 128 / 200, 170 / 369, 334 / 1031; a 500-token prompt
+// (96, 160) 165 / 1190).  Fewer queries only where the call is short and the
+// machine is not full (1 query after 100 tokens (96, 160) 77 / 115), or at
+// r_v > 256 (after 8000 tokens 3010 / 5648).
+bool f32_matrix_prefill(int units, int M, int keys, int r_v) {
+  if (M >= 32 || r_v > 256 || (M >= 16 && r_v > 32)) return true;
+  return keys <= 512 && 2 * units <= lla::device_cu_count();
+}
+
+DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int row_blocks, int r_v) {
   static const int forced_waves = env_int("LLA_DECODE_WAVES");
   static const int forced_splits = env_int("LLA_DECODE_SPLITS");
   static const int forced_deep = env_int("LLA_DECODE_DEEP");
@@ -100,6 +130,13 @@ DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int 
   static const int forced_short_groups = env_int("LLA_DECODE_SHORT_GROUPS");
   const int pages = (n_ctx + LLA_PAGE_TOKENS - 1) / LLA_PAGE_TOKENS;
   const int groups = (pages + 7) / 8;
+  if (!bf16 && !forced_waves && f32_matrix_decode(units, pages, r_v)) {
+    // slices of at least 8 pages, one workgroup per compute unit at most (1500
+    // tokens of two sequences: 3 slices 123 us, 12 of 2 pages 158)
+    long s = allow_split ? std::min<long>(lla::device_cu_count() / units, pages / 8) : 1L;
+    if (forced_splits > 0 && allow_split) s = std::min(forced_splits, max_splits(n_ctx));
+    return DecodeShape{8, (int)std::max(1L, s), 0, 0, 0, 1};
+  }
   const long target = 8L * lla::device_cu_count();  // resident wavefronts wanted
   // bf16: the software-pipelined variant (two batches of loads in flight per
   // wavefront, at most 2 wavefronts per SIMD) measured as fast or faster on
@@ -365,7 +402,7 @@ lla_status lla_decode_splits(int dtype, int B, int H, int n_ctx, int r_k, int r_
       !rank_ok(r_k) || !rank_ok(r_v) || d_rope < 0 || d_rope > LLA_MAX_ROPE)
     return LLA_ERR_INVALID_ARG;
   *splits = choose_shape(B * H, n_ctx, with_workspace != 0, dtype == LLA_BF16,
-                         row_blocks_of(r_k, r_v, d_rope)).splits;
+                         row_blocks_of(r_k, r_v, d_rope), r_v).splits;
   return LLA_OK;
 }
 
@@ -458,12 +495,13 @@ lla_status decode_impl(int dtype, int out_dtype, int B, int H, int d_head, int r
   a.qr = q_rope;
   a.rc = r_cache;
   const DecodeShape sh = choose_shape(B * H, n_ctx, static_scratch || workspace != nullptr,
-                                      dtype == LLA_BF16, row_blocks_of(r_k, r_v, d_rope));
+                                      dtype == LLA_BF16, row_blocks_of(r_k, r_v, d_rope), r_v);
   a.waves = sh.waves;
   a.splits = sh.splits;
   a.deep = sh.deep;
   a.half = sh.half;
   a.shortk = sh.shortk;
+  a.matrix = sh.matrix;
   const hipStream_t st = static_cast<hipStream_t>(stream);
   if (static_scratch) {
     // partials of exactly the chosen split count, in the device's static array
@@ -681,7 +719,8 @@ lla_status prefill_impl(int dtype, int out_dtype, int B, int H, int M, int d_hea
     a.rc = r_cache;
     return hip_status(lla::launch_prefill_bf16(a, static_cast<hipStream_t>(stream)));
   }
-  // fp32: the decode scan, one workgroup per query, query m over [0, p0 + m].
+  // fp32: query m over [0, p0 + m]; the matrix kernel (16 queries per
+  // workgroup) or the decode scan (one workgroup per query).
   lla::DecodeArgs a{};
   a.dtype = dtype;
   a.out_dtype = out_dtype;
@@ -698,6 +737,7 @@ lla_status prefill_impl(int dtype, int out_dtype, int B, int H, int M, int d_hea
   a.splits = 1;
   a.waves = 4;
   a.deep = 0;
+  a.matrix = f32_matrix_prefill(B * H, M, p0 + M, r_v) ? 1 : 0;
   a.q = q;
   a.ck = c_k;
   a.cv = c_v;

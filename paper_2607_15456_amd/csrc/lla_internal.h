@@ -19,6 +19,7 @@ struct DecodeArgs {
   int waves;   // wavefronts per workgroup (4 or 8)
   int deep;    // 1: at most 2 wavefronts per SIMD, 16-row load batches
   int half;    // 1 (bf16, 4 waves, deep): K groups of 4 pages, two feature rows per load
+  int matrix;  // 1 (fp32): the matrix kernel (attn_f32.hip); waves, deep, half and shortk unused
   int shortk;  // 1 (bf16 decode, not split): wavefronts split the rows of each 8-page group
   const int32_t* ctx_len;
   const void* q;
@@ -38,6 +39,8 @@ struct DecodeArgs {
 };
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream);
+// fp32 decode and causal prefill (M queries per (b, h); splits > 1 needs M = 1).
+hipError_t launch_attn_f32(const DecodeArgs& a, hipStream_t stream);
 
 struct EncodeArgs {
   int dtype;

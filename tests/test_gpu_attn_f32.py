@@ -1,0 +1,81 @@
+"""fp32 attention on the matrix instructions (prefill tiles of 16 queries,
+decode over short contexts) against the float64 oracle, at the edges of its
+tiles: query tiles, pages and groups of 8 pages, K batches, 16-row value tiles.
+Latent slots past the context hold NaN throughout."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2607_15456_amd import lla, workloads as W
+from tests.helpers import assert_close, f64, log
+from tests.test_gpu_prefill import SMALL, _case, _oracle
+
+pytestmark = pytest.mark.gpu
+
+DEV, F32 = "cuda", torch.float32
+
+
+@pytest.mark.parametrize("r_k,r_v", [(18, 30), (33, 17), (1, 1), (96, 160), (130, 129), (288, 480), (512, 512)])
+@pytest.mark.parametrize("M,p0", [(16, 0), (17, 47), (15, 63), (33, 500), (1, 511), (40, 1030)])
+def test_prefill_tiles(r_k, r_v, M, p0):
+    log(f"prefill fp32 tiles r=({r_k},{r_v}) M={M} p0={p0}")
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(SMALL, r_k, r_v, 1, M, p0, F32)
+    out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
+    assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, p0), F32, "prefill fp32")
+
+
+@pytest.mark.parametrize("d_head", [32, 96, 256])
+def test_prefill_head_widths(d_head):
+    wl = W.Workload("f32_width", 1, 2, d_head, 4, 1, 0, ((36, 60),), F32)
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, 36, 60, 1, 37, 70, F32)
+    out = lla.prefill_attn(q, pk, pv, uk, uv, p0=70, mu_k=muk, mu_v=muv, out_dtype=F32)
+    assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, 70), F32, f"d={d_head}")
+
+
+@pytest.mark.parametrize("axis", ["k", "v"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+@pytest.mark.parametrize("n_bad", [3, 63, 64, 70, 79])
+def test_nonfinite_reaches_only_its_queries(axis, value, n_bad):
+    """A non-finite latent at position n makes queries n .. non-finite (a value
+    latent; a key latent at least where its score is not -inf) and leaves the
+    queries before n as they are."""
+    r_k, r_v, M = 36, 60, 90
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(SMALL, r_k, r_v, 1, M, 0, F32)
+    ref = _oracle(q, ck, cv, uk, uv, muk, muv, 0)
+    cache = pk if axis == "k" else pv
+    cache[0, 1, n_bad // 64, 5, n_bad % 64] = value
+    out = f64(lla.prefill_attn(q, pk, pv, uk, uv, p0=0, mu_k=muk, mu_v=muv))
+    assert_close(out[:, [0, 2]], ref[:, [0, 2]], F32, "the other heads")
+    assert_close(out[:, 1, :n_bad], ref[:, 1, :n_bad], F32, f"queries before {n_bad}")
+    hit = out[0, 1, n_bad:]
+    if axis == "v" or np.isnan(value):
+        assert not np.any(np.isfinite(hit)), "queries that attend it"
+    else:
+        # an infinite key: a score of +inf gives NaN, one of -inf weight 0
+        kinds = np.isfinite(hit).all(-1) | np.isnan(hit).all(-1)
+        assert kinds.all() and np.isnan(hit).any()
+
+
+@pytest.mark.parametrize("r_k,r_v", [(36, 60), (96, 160), (192, 320)])
+@pytest.mark.parametrize("N,lens", [(64, [64, 1]), (513, [513, 65]), (1500, [1500, 700]), (4000, [3968, 64])])
+@pytest.mark.parametrize("split", [False, True])
+def test_decode_short_contexts(r_k, r_v, N, lens, split):
+    wl = W.Workload("f32_decode", 1, 8, 128, 4, 2, N, ((r_k, r_v),), F32)
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 2, N, 0, F32)
+    q = q[:, :, 0].contiguous()
+    ws = lla.new_workspace(2, 8, r_v, N) if split else None
+    log(f"decode fp32 r=({r_k},{r_v}) N={N} splits={lla.decode_splits(F32, 2, 8, N, r_k, r_v, with_workspace=split)}")
+    for cur in (lens, lens[::-1]):
+        out = lla.decode_attn(q, pk, pv, uk, uv, n_ctx=N, ctx_len=torch.tensor(cur, dtype=torch.int32, device=DEV),
+                              mu_k=muk, mu_v=muv, workspace=ws)
+        ref = np.concatenate([oracle.decode_attn_batched(f64(q)[b:b + 1], f64(ck)[b:b + 1], f64(cv)[b:b + 1], f64(uk),
+                                                         f64(uv), f64(muk), f64(muv), None, ctx_len=cur[b])
+                              for b in range(2)])
+        assert_close(f64(out), ref, F32, f"lens={cur}")
+    bad = lla.decode_attn(q, pk, pv, uk, uv, n_ctx=N, ctx_len=torch.tensor([0, N + 1], dtype=torch.int32, device=DEV),
+                          workspace=ws)
+    assert bool(torch.isnan(bad).all())
+    if split:
+        assert int(ws[:4 * 2 * 8].view(torch.int32).abs().sum()) == 0
