@@ -15,6 +15,8 @@
 //
 // fp32: the same product on the fp32 matrix instructions, 32 x 32 tiles.
 
+#include <type_traits>
+
 #include "lla_device.h"
 #include "lla_internal.h"
 #include "../../include/lla.h"
@@ -357,253 +359,319 @@ __global__ __launch_bounds__(256) void encode_few_kernel(EncodeArgs a, int nrc_k
   }
 }
 
-// Prefill-sized writes over a long stack (the LLA-2D down-projection, K =
-// T*H*d = 8192 values into r = 288 / 480): 2 r flops per byte of x, a
-// compute-bound GEMM.  A workgroup of 8 wavefronts takes 256 tokens x 96 rows
-// of one axis; both operands are staged through double-buffered LDS in K-chunks
-// of 64 (two further chunks in flight in registers), and wavefront w computes
-// tokens 32w .. 32w + 31 x all 96 rows on v_mfma_f32_32x32x16_bf16:
+// Writes of many tokens: 2 r flops per byte of x, a GEMM.  A workgroup of 4
+// wavefronts takes 128 XT tokens x up to 96 rows of one axis, wavefront w tokens
+// 32 XT w .. x all rows on v_mfma_f32_32x32x16_bf16:
 //   keys   (token-major cache): D = C^T (M = row, N = token), a lane holds
 //          4-row runs of one token;
-//   values (feature-major pages): D = C (M = token, N = row).
+//   values, per-head keys (feature-major pages): D = C (M = token, N = row).
+// Weights pass through double-buffered LDS chunks of 64 values, read by every
+// wavefront.  A token belongs to one wavefront: its x passes through a region
+// of LDS that only this wavefront uses (a wave-wide load covers 8 tokens x 128
+// bytes; straight to the operand registers each lane's 16 bytes were a cache
+// line of their own, which bound the loop), with one or two further chunks in
+// registers and no barrier.  5 KB of LDS reads feed 6 products, where one
+// 32-token tile per wavefront took 4 KB for 3; two workgroups share a compute
+// unit.
 // The row blocks of one token block are dispatched back to back on one XCD
-// (workgroup i runs on XCD i % 8), so its x chunks come from that XCD's L2
-// after the first read.  With a mean, wavefronts 0 .. 2 also form W_down^T mu
-// for one 32-row tile each (mu as a broadcast operand), shared through LDS.
-constexpr int kGTok = 256, kGRow = 96, kGKC = 64, kGS = kGKC + 8;
-constexpr int kGTS = kGTok + 8;  // row stride (bf16) of the epilogue's output tile in LDS
-constexpr int kGThreads = 512;
+// (workgroup i runs on XCD i % 8), so its x comes from that XCD's L2 after the
+// first read.  W_down^T mu is formed on the vector unit from the staged weights.
+// Measured against one 8-wavefront workgroup of 256 x 96 per compute unit with
+// both operands in shared LDS: 2 x 3001 tokens (192, 320) with means 227 -> 130
+// us (a read of x at the copy rate is 76), 4 x 8192 (288, 480) 1131 -> 799 us
+// (516 TFLOP/s), 300 tokens (96, 160) 35 -> 20, the LLA-2D stack (K = 8192) 2 x
+// 4096 tokens 152 -> 137 us (753 TFLOP/s).  LDS reads and the matrix units now
+// take about the same time.
+constexpr int kGRow = 96, kGKC = 64, kGS = kGKC + 8;
+constexpr int kGThreads = 256;
+template <int XT>
+constexpr int kGRing = XT == 2 ? 1 : 2;
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+template <int XT>
+struct GemmLds {
+  __attribute__((aligned(16))) bf16_t x[4][32 * XT * kGS];  // each wavefront's tokens, one chunk
+  __attribute__((aligned(16))) bf16_t w[2][kGRow * kGS];
+  __attribute__((aligned(16))) bf16_t mu[2][kGKC];
+  float wmu[kGRow];                                       // W_down^T mu of the current head
+  __attribute__((aligned(16))) bf16_t tile[4][32 * 40];   // epilogue tile of each wavefront
+};
+
 // AXIS: 0 keys, 1 values.  TM: the output cache is token-major (the LLA-2D key
 // cache); the products then hold rows in a lane's registers (one token per
 // lane), stored as 8 bytes of 4 consecutive features.  Otherwise a lane's
 // register groups hold 4 consecutive tokens of one row, and the tile reaches
-// the feature-major pages through LDS as whole 128-byte page rows.
-template <int AXIS, bool TM>
-__device__ __forceinline__ void encode_gemm_body(const EncodeArgs& a, int tb, int rb, int h0, int nh,
-                                                 bf16_t (*s_x)[kGTok * kGS], bf16_t (*s_w)[kGRow * kGS],
-                                                 float* s_mu, bf16_t* s_t) {
+// the feature-major pages through LDS as 16-byte pieces of whole page rows.
+// RT: 32-row tiles.  The workgroup walks heads h0 .. h0 + nh - 1 as one stream
+// of K-chunks, so a head's first loads are in flight while the previous head
+// finishes.
+template <int AXIS, bool TM, int RT, int XT>
+__device__ __forceinline__ void encode_gemm_body(const EncodeArgs& a, int tfirst, int tlo, int thi, int row0, int h0, int nh,
+                                                 GemmLds<XT>& s) {
+  constexpr int NR = kGRing<XT>;  // chunks of x in registers
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int col = lane & 31, g = lane >> 5;
-  constexpr int axis = AXIS;
-  const int row0 = rb * kGRow;
-  const int r = pick(a.r, axis), K = a.K, H = a.H;
-  const int TT = a.B * a.M, t0 = tb * kGTok;
-  const bf16_t* xg = static_cast<const bf16_t*>(pick(a.x, axis));
-  const bf16_t* wg = static_cast<const bf16_t*>(pick(a.wdt, axis));
-  // The workgroup walks heads h0 .. h0 + nh - 1 as one stream of K-chunks
-  // (chunk q: head h0 + q / nkc, K offset (q % nkc) * kGKC), so the loads of a
-  // head's first chunks are in flight while the previous head finishes.
+  const int r = pick(a.r, AXIS), K = a.K, H = a.H;
+  const int t0 = tfirst + wave * 32 * XT;
+  const bf16_t* mug = static_cast<const bf16_t*>(pick(a.mu, AXIS));
+  const bool mu = mug != nullptr;  // uniform
   const int nkc = K / kGKC, total = nh * nkc;
 
-  // staging: x chunk = 256 tokens x 64 (4 chunks of 16 bytes per thread),
-  // W chunk = 96 rows x 64 (768 chunks: threads 0 .. 255 take two)
-  uint4 sxa[4], swa[2], sxb[4], swb[2];  // two register sets, named at compile time
-  auto load = [&](int q, uint4 (&sx)[4], uint4 (&sw)[2]) {
-    const int hq = q / nkc, hh = h0 + hq, k0 = (q - hq * nkc) * kGKC;
+  // x: the heads of a token are adjacent, so chunk q of the stream is at 64 q;
+  // lane (token lane / 8 of 8, piece lane % 8).  Tokens outside [tlo, thi)
+  // re-read one inside: their columns are never stored.
+  const bf16_t* xp[4 * XT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = tid + i * kGThreads, tok = c >> 3, part = c & 7, t = t0 + tok;
-      sx[i] = ld16(xg + ((size_t)(t < TT ? t : TT - 1) * H + hh) * K + k0 + 8 * part);
+  for (int i = 0; i < 4 * XT; ++i)
+    xp[i] = static_cast<const bf16_t*>(pick(a.x, AXIS)) +
+            ((size_t)max(tlo, min(t0 + 8 * i + (lane >> 3), thi - 1)) * H + h0) * K + 8 * (lane & 7);
+  uint4 x[NR][4 * XT];
+  auto xload = [&](uint4 (&v)[4 * XT], int q) {
+    const int o = kGKC * min(q, total - 1);
+#pragma unroll
+    for (int i = 0; i < 4 * XT; ++i) v[i] = ld16(xp[i] + o);
+  };
+  bf16_t* const xs = s.x[wave];
+  auto xstore = [&](const uint4 (&v)[4 * XT]) {
+#pragma unroll
+    for (int i = 0; i < 4 * XT; ++i)
+      *reinterpret_cast<uint4*>(&xs[(8 * i + (lane >> 3)) * kGS + 8 * (lane & 7)]) = v[i];
+  };
+  // W chunk: RT * 32 rows x 64, RT 16-byte pieces per thread; the mean's 64
+  // values, one piece of threads 0 .. 7
+  uint4 sw[RT], sm = make_uint4(0, 0, 0, 0);
+  int lh = h0, lk = 0;  // head and K-chunk of the next W load
+  auto wload = [&]() {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const int row = min(row0 + 32 * i + (tid >> 3), r - 1);  // rows past the rank: never stored
+      sw[i] = ld16(static_cast<const bf16_t*>(pick(a.wdt, AXIS)) + ((size_t)lh * r + row) * K + lk * kGKC + 8 * (tid & 7));
     }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * kGThreads, row = row0 + (c >> 3), part = c & 7;
-      sw[i] = ld16(wg + ((size_t)hh * r + (row < r ? row : r - 1)) * K + k0 + 8 * part);
+    if (mu && tid < 8) sm = ld16(mug + (size_t)lh * K + lk * kGKC + 8 * tid);
+    if (lk + 1 < nkc) {
+      ++lk;
+    } else if (lh + 1 < h0 + nh) {  // the last chunk is re-read, not multiplied
+      lk = 0;
+      ++lh;
     }
   };
-  auto store = [&](const uint4 (&sx)[4], const uint4 (&sw)[2], int buf) {
+  auto wstore = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int c = tid + i * kGThreads, tok = c >> 3, part = c & 7;
-      *reinterpret_cast<uint4*>(&s_x[buf][tok * kGS + 8 * part]) = t0 + tok < TT ? sx[i] : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int c = tid + i * kGThreads, rr = c >> 3, part = c & 7;
-      if (c < kGRow * 8)
-        *reinterpret_cast<uint4*>(&s_w[buf][rr * kGS + 8 * part]) = row0 + rr < r ? sw[i] : make_uint4(0, 0, 0, 0);
-    }
+    for (int i = 0; i < RT; ++i)
+      *reinterpret_cast<uint4*>(&s.w[buf][(32 * i + (tid >> 3)) * kGS + 8 * (tid & 7)]) = sw[i];
+    if (mu && tid < 8) *reinterpret_cast<uint4*>(&s.mu[buf][8 * tid]) = sm;
   };
 
-  f32x16 acc[3], accm = f32x16{0.f};
+  f32x16 acc[XT][RT];
 #pragma unroll
-  for (int rt = 0; rt < 3; ++rt) acc[rt] = f32x16{0.f};
-  const bool mu = pick(a.mu, axis) != nullptr;  // uniform
-  const bf16_t* mug = mu ? static_cast<const bf16_t*>(pick(a.mu, axis)) + 8 * g : nullptr;
+  for (int u = 0; u < XT; ++u)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) acc[u][rt] = f32x16{0.f};
+  float wmu = 0.f;  // row tid / 2, half tid % 2 of every chunk
 
-  auto chunk = [&](int q, int buf) {
-    const bf16_t* xs = &s_x[buf][(32 * wave + col) * kGS + 8 * g];
-    const bf16_t* ws = &s_w[buf][col * kGS + 8 * g];
+  auto chunk = [&](int buf) {
+    const bf16_t* ws = &s.w[buf][col * kGS + 8 * g];
+    const bf16_t* xr = &xs[col * kGS + 8 * g];
 #pragma unroll
-    for (int s = 0; s < kGKC / 16; ++s) {
-      const bf16x8 xo = as_bf16x8(*reinterpret_cast<const uint4*>(xs + 16 * s));
+    for (int k = 0; k < 4; ++k) {
+      bf16x8 wo[RT], xo[XT];
 #pragma unroll
-      for (int rt = 0; rt < 3; ++rt) {
-        const bf16x8 wo = as_bf16x8(*reinterpret_cast<const uint4*>(ws + 32 * rt * kGS + 16 * s));
-        acc[rt] = TM ? mfma32(wo, xo, acc[rt]) : mfma32(xo, wo, acc[rt]);
+      for (int u = 0; u < XT; ++u) xo[u] = as_bf16x8(*reinterpret_cast<const uint4*>(xr + 32 * u * kGS + 16 * k));
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) wo[rt] = as_bf16x8(*reinterpret_cast<const uint4*>(ws + 32 * rt * kGS + 16 * k));
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int u = 0; u < XT; ++u)
+          acc[u][rt] = TM ? mfma32(wo[rt], xo[u], acc[u][rt]) : mfma32(xo[u], wo[rt], acc[u][rt]);
+    }
+  };
+  auto mean = [&](int buf) {
+    if (mu && tid < 64 * RT) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float wv[8], mv[8];
+        Elem<bf16_t>::unpack(*reinterpret_cast<const uint4*>(&s.w[buf][(tid >> 1) * kGS + 32 * (tid & 1) + 8 * k]), wv);
+        Elem<bf16_t>::unpack(*reinterpret_cast<const uint4*>(&s.mu[buf][32 * (tid & 1) + 8 * k]), mv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wmu = fmaf(wv[e], mv[e], wmu);
       }
     }
-    // the mean's products in one block after the chunk's (a guard inside the
-    // K-step loop made each of them a block of its own)
-    if (mu && wave < 3) {
-      uint4 wm[kGKC / 16], mo[kGKC / 16];
-#pragma unroll
-      for (int s = 0; s < kGKC / 16; ++s) {
-        wm[s] = *reinterpret_cast<const uint4*>(ws + 32 * wave * kGS + 16 * s);
-        mo[s] = ld16(mug + (size_t)(h0 + q / nkc) * K + (q % nkc) * kGKC + 16 * s);
-      }
-#pragma unroll
-      for (int s = 0; s < kGKC / 16; ++s) accm = mfma32(as_bf16x8(wm[s]), as_bf16x8(mo[s]), accm);
-    }
+  };
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
 
-  // head hh done: the mean's products to LDS, the tile to the cache, then the
-  // accumulators cleared for the next head
+  // head hh done: the tile to the cache, then the accumulators cleared
   auto finish = [&](int hh_) {
     // Opaque copies: the epilogue's row and token bookkeeping is then formed
     // here, per head, instead of being hoisted out of the head loop, where it
     // would hold registers across every chunk.
-    int hh = hh_, r = pick(a.r, axis), row0 = rb * kGRow, t0 = tb * kGTok;
-    asm volatile("" : "+s"(hh), "+s"(r), "+s"(row0), "+s"(t0));
+    int hh = hh_, r = pick(a.r, AXIS), rw = row0, tw = t0;
+    asm volatile("" : "+s"(hh), "+s"(r), "+s"(rw), "+s"(tw));
     if (mu) {
-      // accm (M = row of tile `wave`, N = any column): rows 8(q/4) + 4g + q%4
-      if (wave < 3 && col == 0) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) s_mu[32 * wave + 8 * (q / 4) + 4 * g + q % 4] = accm[q];
-      }
+      wmu += xor_shfl(wmu, 1);
+      if (tid < 64 * RT && (tid & 1) == 0) s.wmu[tid >> 1] = wmu;
+      wmu = 0.f;
       __syncthreads();
     }
-
-    bf16_t* cout = static_cast<bf16_t*>(pick(a.c, axis));
+    bf16_t* cout = static_cast<bf16_t*>(pick(a.c, AXIS));
     if constexpr (TM) {
       // lane (token col, half g), register q of row tile rt: row 32 rt + 8(q/4) + 4g + q%4
-      const int t = t0 + 32 * wave + col;
-      if (t < TT) {
-        const int b = t / a.M, pos = ring_slot(a.pos0 + (t - b * a.M), a.sink, a.window);
 #pragma unroll
-        for (int rt = 0; rt < 3; ++rt)
+      for (int u = 0; u < XT; ++u) {
+        const int t = tw + 32 * u + col;
+        if (t >= tlo && t < thi) {
+          const int b = t / a.M, pos = ring_slot(a.pos0 + (t - b * a.M), a.sink, a.window);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int rl = 32 * rt + 8 * i + 4 * g, row = row0 + rl;  // first of 4 consecutive rows
-            if (row + 3 < r) {
-              // token-major cache: the 4 rows are contiguous, 8-byte aligned (r_k % 32 == 0)
-              const uint32_t lo = uint32_t(f32_to_bf16(acc[rt][4 * i] - (mu ? s_mu[rl] : 0.f))) |
-                                  (uint32_t(f32_to_bf16(acc[rt][4 * i + 1] - (mu ? s_mu[rl + 1] : 0.f))) << 16);
-              const uint32_t hi = uint32_t(f32_to_bf16(acc[rt][4 * i + 2] - (mu ? s_mu[rl + 2] : 0.f))) |
-                                  (uint32_t(f32_to_bf16(acc[rt][4 * i + 3] - (mu ? s_mu[rl + 3] : 0.f))) << 16);
-              *reinterpret_cast<uint2*>(&cout[cache_index(b, hh, H, a.n_max, r, pos, row, true)]) = make_uint2(lo, hi);
-            } else {
+          for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (row + e < r)
-                  cout[cache_index(b, hh, H, a.n_max, r, pos, row + e, true)] =
-                      f32_to_bf16(acc[rt][4 * i + e] - (mu ? s_mu[rl + e] : 0.f));
+            for (int i = 0; i < 4; ++i) {
+              const int rl = 32 * rt + 8 * i + 4 * g, row = rw + rl;  // first of 4 consecutive rows
+              bf16_t v[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] = f32_to_bf16(acc[u][rt][4 * i + e] - (mu ? s.wmu[rl + e] : 0.f));
+              bf16_t* dst = &cout[cache_index(b, hh, H, a.n_max, r, pos, row, true)];
+              if (row + 3 < r)  // the 4 rows are contiguous, 8-byte aligned (r_k % 32 == 0)
+                *reinterpret_cast<uint2*>(dst) = make_uint2(v[0] | (uint32_t(v[1]) << 16), v[2] | (uint32_t(v[3]) << 16));
+              else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                  if (row + e < r) dst[e] = v[e];
             }
-          }
-      }
-    } else {
-      // lane (row col of tile rt, half g), register q: token 32 wave + 8(q/4) + 4g + q%4,
-      // so registers 4i .. 4i + 3 are 4 consecutive tokens of one feature row.
-      // The tile goes through LDS as [row][token] bf16, then runs of 8 threads
-      // store a row's 64 tokens of one page as 128 contiguous bytes (16 bytes
-      // each) when the slots are 8 consecutive positions of one sequence (no
-      // ring, a position a multiple of 8), else one element at a time.
-#pragma unroll
-      for (int rt = 0; rt < 3; ++rt) {
-        const int rl = 32 * rt + col;
-        const float m = mu ? s_mu[rl] : 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const uint32_t lo = uint32_t(f32_to_bf16(acc[rt][4 * i] - m)) |
-                              (uint32_t(f32_to_bf16(acc[rt][4 * i + 1] - m)) << 16);
-          const uint32_t hi = uint32_t(f32_to_bf16(acc[rt][4 * i + 2] - m)) |
-                              (uint32_t(f32_to_bf16(acc[rt][4 * i + 3] - m)) << 16);
-          *reinterpret_cast<uint2*>(&s_t[rl * kGTS + 32 * wave + 8 * i + 4 * g]) = make_uint2(lo, hi);
         }
       }
-      __syncthreads();
-      constexpr int kItems = kGRow * (kGTok / 8) / kGThreads;  // 16-byte pieces per thread
+    } else {
+      // lane (row col of tile rt, half g), register q: token 8(q/4) + 4g + q%4
+      // of a 32-token tile, so registers 4i .. 4i + 3 are 4 consecutive tokens
+      // of one feature row.  Each wavefront turns a row tile through its own
+      // LDS tile [row][token]; runs of 4 lanes then store a row's tokens 16
+      // bytes each when their slots are 8 consecutive ones of one sequence from
+      // a multiple of 8, else one element at a time.
+      bf16_t* tile = s.tile[wave];
 #pragma unroll
-      for (int k = 0; k < kItems; ++k) {
-        const int item = tid + k * kGThreads, rl = item / (kGTok / 8), grp = item % (kGTok / 8);
-        const int row = row0 + rl;
-        if (row >= r) continue;
-        const uint4 v = *reinterpret_cast<const uint4*>(&s_t[rl * kGTS + 8 * grp]);
-        const int t = t0 + 8 * grp;  // first token of the piece
-        const int b = t / a.M, m0 = t - b * a.M, p = a.pos0 + m0;
-        if (a.window == 0 && t + 7 < TT && m0 + 7 < a.M && (p & 7) == 0) {
-          *reinterpret_cast<uint4*>(&cout[cache_index(b, hh, H, a.n_max, r, p, row)]) = v;
-        } else {
-          const bf16_t* e8 = reinterpret_cast<const bf16_t*>(&v);
+      for (int rt = 0; rt < RT; ++rt) {
+        const float m = mu ? s.wmu[32 * rt + col] : 0.f;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int te = t + e;
-            if (te < TT) {
-              const int be = te / a.M, pos = ring_slot(a.pos0 + (te - be * a.M), a.sink, a.window);
-              cout[cache_index(be, hh, H, a.n_max, r, pos, row)] = e8[e];
+        for (int u = 0; u < XT; ++u) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            uint32_t v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = f32_to_bf16(acc[u][rt][4 * i + e] - m);
+            *reinterpret_cast<uint2*>(&tile[col * 40 + 8 * i + 4 * g]) = make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
+          }
+          wave_sync();
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const int rl = (lane >> 2) + 16 * k, grp = lane & 3, row = rw + 32 * rt + rl;
+            const int t = tw + 32 * u + 8 * grp;  // first token of the piece
+            if (row >= r || t + 7 < tlo || t >= thi) continue;
+            const int b = t / a.M, m0 = t - b * a.M;
+            const int p = ring_slot(a.pos0 + m0, a.sink, a.window);
+            if (t >= tlo && t + 7 < thi && m0 + 7 < a.M && (p & 7) == 0 &&
+                ring_slot(a.pos0 + m0 + 7, a.sink, a.window) == p + 7) {
+              *reinterpret_cast<uint4*>(&cout[cache_index(b, hh, H, a.n_max, r, p, row)]) =
+                  *reinterpret_cast<const uint4*>(&tile[rl * 40 + 8 * grp]);
+            } else {
+#pragma unroll 1
+              for (int te = max(t, tlo); te < min(t + 8, thi); ++te) {
+                const int be = te / a.M, pos = ring_slot(a.pos0 + (te - be * a.M), a.sink, a.window);
+                cout[cache_index(be, hh, H, a.n_max, r, pos, row)] = tile[rl * 40 + 8 * grp + te - t];
+              }
             }
           }
+          wave_sync();
         }
       }
     }
 #pragma unroll
-    for (int rt = 0; rt < 3; ++rt) acc[rt] = f32x16{0.f};
-    accm = f32x16{0.f};
+    for (int u = 0; u < XT; ++u)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[u][rt] = f32x16{0.f};
   };
 
-  // set a holds even chunks, set b odd ones; chunk q is in LDS buffer q % 2
-  // (nkc is even whenever a workgroup takes more than one head, so every head
-  // starts on set a).  Each head's last chunk is followed, after the barrier,
-  // by its epilogue; the barriers of the next head's chunks order its use of
-  // LDS against the next epilogue.
-  load(0, sxa, swa);
-  load(total > 1 ? 1 : 0, sxb, swb);
-  store(sxa, swa, 0);
+  // Chunk q's weights are in LDS buffer q % 2, its x in the wavefront's region,
+  // chunks q + 1 .. q + NR of x in registers (q + 1 in slot q % NR; nkc is a
+  // multiple of NR whenever a workgroup takes more than one head).  W chunk
+  // q + 1 is stored to the buffer that chunk q - 1 left, after chunk q's
+  // products; x chunk q + 1 after them in the wavefront's own order.
+  wload();
+  xload(x[NR - 1], 0);
+  wstore(0);
+  xstore(x[NR - 1]);
+  wload();
+#pragma unroll
+  for (int q = 0; q < NR; ++q) xload(x[q], q + 1);
   __syncthreads();
-  for (int hq = 0; hq < nh; ++hq) {
-    const int qe = (hq + 1) * nkc;  // end of this head's chunks
-    for (int q = hq * nkc; q < qe; q += 2) {
-      load(min(q + 2, total - 1), sxa, swa);
-      chunk(q, 0);
-      if (q + 1 < total) store(sxb, swb, 1);
-      __syncthreads();
-      if (q + 1 < qe) {
-        load(min(q + 3, total - 1), sxb, swb);
-        chunk(q + 1, 1);
-        if (q + 2 < total) store(sxa, swa, 0);
-        __syncthreads();
+  for (int hq = 0, q = 0; hq < nh; ++hq) {
+    for (int kc = 0; kc < nkc; kc += NR, q += NR) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        if (kc + i < nkc) {
+          const int buf = (q + i) & 1;
+          chunk(buf);
+          wave_sync();
+          xstore(x[i]);
+          xload(x[i], q + i + 1 + NR);
+          mean(buf);
+          wstore(buf ^ 1);
+          wload();
+          __syncthreads();
+        }
       }
     }
     finish(h0 + hq);
   }
 }
 
-// Both axes in one launch (1024 equal workgroups for the 2D prompt write of
-// 4 x 8192 tokens: four full rounds of the machine).  XCD-aware order: the
-// j-th workgroup of XCD x takes token block x + 8 (j / nrb) and row block
-// j % nrb (the row blocks of axis k, then those of axis v).
+// Both axes in one launch.  XCD-aware order: the j-th workgroup of XCD x takes
+// token block x + 8 (j / nrb) and row block j % nrb (the row blocks of axis k,
+// then those of axis v).  An axis of n 32-row tiles is cut into ceil(n / 3)
+// blocks of 3, 2 or 1 tiles (160 rows: 3 + 2; 320: 3 + 3 + 2 + 2).
+template <int XT>
 __global__ __launch_bounds__(kGThreads) __attribute__((amdgpu_waves_per_eu(2)))
-void encode_gemm_kernel(EncodeArgs a, int nrb_k, int nrb, int ntb, int hpw) {
-  __shared__ __attribute__((aligned(16))) bf16_t s_x[2][kGTok * kGS];
-  __shared__ __attribute__((aligned(16))) bf16_t s_w[2][kGRow * kGS];
-  __shared__ float s_mu[kGRow];
-  __shared__ __attribute__((aligned(16))) bf16_t s_t[kGRow * kGTS];  // epilogue tile (feature-major outputs)
+void encode_gemm_kernel(EncodeArgs a, int nrb_k, int nrb, int ntb, int nsb, int hpw) {
+  __shared__ GemmLds<XT> s;
   const int xcd = blockIdx.x % 8, j = blockIdx.x / 8;
   const int tb = xcd + 8 * (j / nrb), rb = j % nrb;
   if (tb >= ntb) return;  // padding of the grid to whole rounds of 8 token blocks
+  // nsb blocks per sequence, cut at cache slots that are multiples of the block
+  // (the pieces of the epilogue then start on 16 bytes whatever M and pos0
+  // are), or (nsb 0) blocks of the flattened tokens
+  int tfirst = tb * 128 * XT, tlo = 0, thi = a.B * a.M;
+  if (nsb) {
+    const int b = tb / nsb;
+    tlo = b * a.M;
+    thi = tlo + a.M;
+    tfirst = tlo + (tb - b * nsb) * 128 * XT - (a.pos0 & 7);
+  }
   const int h0 = blockIdx.y * hpw, nh = min(hpw, a.H - h0);  // a run of heads
-  if (rb >= nrb_k)
-    encode_gemm_body<1, false>(a, tb, rb - nrb_k, h0, nh, s_x, s_w, s_mu, s_t);
+  const int axis = rb >= nrb_k ? 1 : 0, blocks = axis ? nrb - nrb_k : nrb_k, i = rb - axis * nrb_k;
+  const int nt = (pick(a.r, axis) + 31) / 32;  // tiles of the axis
+  const int f0 = i * nt / blocks, rt = (i + 1) * nt / blocks - f0;
+  auto run = [&](auto ax, auto tm) {
+    constexpr int A = decltype(ax)::value;
+    constexpr bool T = decltype(tm)::value;
+    if (rt == 3)
+      encode_gemm_body<A, T, 3, XT>(a, tfirst, tlo, thi, 32 * f0, h0, nh, s);
+    else if (rt == 2)
+      encode_gemm_body<A, T, 2, XT>(a, tfirst, tlo, thi, 32 * f0, h0, nh, s);
+    else
+      encode_gemm_body<A, T, 1, XT>(a, tfirst, tlo, thi, 32 * f0, h0, nh, s);
+  };
+  if (axis)
+    run(std::integral_constant<int, 1>{}, std::false_type{});
   else if (a.k_token_major)
-    encode_gemm_body<0, true>(a, tb, rb, h0, nh, s_x, s_w, s_mu, s_t);
+    run(std::integral_constant<int, 0>{}, std::true_type{});
   else
-    encode_gemm_body<0, false>(a, tb, rb, h0, nh, s_x, s_w, s_mu, s_t);
+    run(std::integral_constant<int, 0>{}, std::false_type{});
 }
 
 // Second launch of a split write: tile unit (grid x, y, z as the split launch
@@ -641,8 +709,8 @@ __global__ __launch_bounds__(256) void encode_reduce_kernel(EncodeArgs a, int nr
 // sums in fp32).  Workgroup = 32 rows x 32 tokens of one (axis, head); its four
 // wavefronts split K in turn, 16 values at a time, each with a 2 x 2 block of
 // 16x16 tiles: a lane's 16 bytes (row or token lane % 16, values 4 (lane / 16) ..)
-// are the operands of four products, straight from memory, so an operand is
-// loaded twice per product pair instead of once.  The four partial blocks add
+// are the operands of four products with both tiles of the other side,
+// straight from memory.  The four partial blocks add
 // through LDS in wavefront order, and a row of 32 tokens leaves as 128
 // consecutive bytes.  x - mu is formed in fp32 before the product.
 // grid: x = token block x row block (axis k, then v), y = head; a head's
@@ -713,9 +781,12 @@ __global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a, int nrc_k
 
 }  // namespace
 
-static int gemm_heads_per_wg(int H, int blocks, int nkc) {
-  if (nkc % 2) return 1;  // a run of heads needs every head to start on the same register set
-  const int hpw = (int)((int64_t)H * blocks / 1024);
+// Heads per workgroup: as many as keep at least 2048 workgroups (four rounds of
+// the machine), so short stacks (per-head writes) do not pay the pipeline fill
+// per head.
+static int gemm_heads_per_wg(int H, int blocks, int nkc, int ring) {
+  if (nkc % ring) return 1;  // a run of heads needs every head to start on the same register set
+  const int hpw = (int)((int64_t)H * blocks / 2048);
   return hpw < 1 ? 1 : hpw > H ? H : hpw;
 }
 
@@ -761,18 +832,35 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((encode_stream_kernel<8>), grid, dim3(256), 0, stream, a, bpw);
       return hipGetLastError();
     }
-    if (TT >= kGTok && a.K % kGKC == 0 && (a.K >= 2048 || rmax > 64)) {
-      // prefill-sized write over a long stack (the LLA-2D down-projection), or
-      // at ranks above the streaming kernel's (the per-head tiers): a GEMM
-      // tiled for the MFMAs, x re-read from L2 per row block
-      const int ntb = (TT + kGTok - 1) / kGTok, ntb8 = (ntb + 7) / 8 * 8;
+    // Many tokens: the GEMM from 256 tokens (512 at ranks up to 64, whose
+    // weights the 32-token kernel re-reads cheaply; 192 above 64 over a per-head
+    // stack), measured GEMM / 32-token kernel at K = 512: 200 tokens (96, 160)
+    // 18.0 / 19.4 us, (288, 480) 29.5 / 41.5; 130 tokens 16.1 / 13.5; (36, 60)
+    // 300 tokens 12.7 / 12.0, 3000 tokens 26.4 / 75.7.
+    const int gemm_from = a.K >= 2048 ? 256 : rmax > 64 ? 192 : 512;
+    if (TT >= gemm_from && a.K % kGKC == 0) {
       const int nrb_k = (a.r[0] + kGRow - 1) / kGRow, nrb = nrb_k + (a.r[1] + kGRow - 1) / kGRow;
-      // heads per workgroup: as many as keep at least 1024 workgroups (four
-      // rounds of the machine), so short stacks (per-head writes) do not pay
-      // the pipeline fill and the epilogue per head on their own
-      const int hpw = gemm_heads_per_wg(a.H, nrb * ntb8, a.K / kGKC);
-      hipLaunchKernelGGL(encode_gemm_kernel, dim3(nrb * ntb8, (a.H + hpw - 1) / hpw), dim3(kGThreads), 0, stream, a,
-                         nrb_k, nrb, ntb, hpw);
+      auto launch = [&](auto xt) {
+        constexpr int XT = decltype(xt)::value;
+        // blocks cut per sequence unless that fills them badly (short sequences)
+        int nsb = (a.M + (a.pos0 & 7) + 128 * XT - 1) / (128 * XT), ntb = (TT + 128 * XT - 1) / (128 * XT);
+        if ((int64_t)nsb * a.B <= ntb + ntb / 8 + 1)
+          ntb = nsb * a.B;
+        else
+          nsb = 0;
+        const int ntb8 = (ntb + 7) / 8 * 8;
+        const int hpw = gemm_heads_per_wg(a.H, nrb * ntb, a.K / kGKC, kGRing<XT>);
+        hipLaunchKernelGGL((encode_gemm_kernel<XT>), dim3(nrb * ntb8, (a.H + hpw - 1) / hpw), dim3(kGThreads), 0,
+                           stream, a, nrb_k, nrb, ntb, nsb, hpw);
+      };
+      // 64 tokens per wavefront where that leaves two workgroups per compute
+      // unit to take (2 x 3001 tokens (192, 320) 130 us, 32 per wavefront 158),
+      // else 32 (300 tokens (96, 160) 20 us, 64 per wavefront 31)
+      const bool wide = (int64_t)((TT + 255) / 256) * nrb * a.H >= 2 * device_cu_count();
+      if (wide)
+        launch(std::integral_constant<int, 2>{});
+      else
+        launch(std::integral_constant<int, 1>{});
       return hipGetLastError();
     }
     const int heads_per_wg = blocks >= 256 ? a.H : 1;

@@ -220,3 +220,46 @@ def test_fp32_tiles(r_k, r_v, M, pos0, d_head):
     log(f"encode fp32 r=({r_k},{r_v}) M={M} pos0={pos0} d={d_head}")
     inputs, ck, cv = _run(wl, r_k, r_v, 3, M, pos0, 192, True, torch.float32)
     _check(wl, inputs, ck, cv, pos0, M, torch.float32, "fp32 tiles")
+
+
+@pytest.mark.parametrize("r_k,r_v", [(33, 65), (160, 97), (96, 320), (36, 60)])
+@pytest.mark.parametrize("B,M,pos0,T,d_head", [(1, 192, 0, 4, 128), (3, 171, 5, 4, 128), (2, 601, 61, 2, 96),
+                                               (40, 13, 7, 1, 64), (2, 1500, 3, 4, 128)])
+@pytest.mark.parametrize("means", [False, True])
+def test_gemm_tiles(r_k, r_v, B, M, pos0, T, d_head, means):
+    """The GEMM write at the edges of its blocks: row blocks of 3, 2 and 1
+    tiles, token blocks cut per sequence (odd lengths and positions) and over
+    short sequences, an odd number of K-chunks (K = 192), one chunk (K = 64),
+    32 and 64 tokens per wavefront."""
+    wl = W.Workload("enc_gemm", 1, 16 if M == 1500 else 3, d_head, T, B, 0, ((18, 30),), torch.bfloat16)
+    n_max = (pos0 + M + 63) // 64 * 64 + 64
+    log(f"encode gemm r=({r_k},{r_v}) B={B} M={M} pos0={pos0} K={T * d_head} means={means}")
+    (xk, xv, wk, wv, muk, muv), ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, means, torch.bfloat16)
+    for x, w, mu, c in ((xk, wk, muk, ck), (xv, wv, muv, cv)):
+        ref = oracle.encode_batched(f64(x), None if mu is None else f64(mu), f64(w))
+        got = f64(lla.from_paged(c))
+        new = got[:, :, pos0:pos0 + M]
+        # the stored value is the fp32 sum rounded to bf16: half an ulp is at most
+        # 2^-8 of the value; the sums themselves (512 terms of variance 1/512, with
+        # the mean's subtracted) are good to 1e-3 by far
+        assert np.all(np.abs(new - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-3)
+        assert np.all(got[:, :, :pos0] == SENTINEL) and np.all(got[:, :, pos0 + M:] == SENTINEL)
+
+
+@pytest.mark.parametrize("pos0", [0, 203, 1001])
+def test_gemm_ring(pos0):
+    """The GEMM write into a sink + window budget: pieces that are 8 consecutive
+    aligned slots, and those that cross the ring's end or the sink."""
+    wl = W.Workload("enc_ring", 1, 3, 128, 4, 2, 0, ((18, 30),), torch.bfloat16)
+    B, M, r_k, r_v, sink, window = 2, 350, 96, 160, 4, 380
+    xk, xv, wk, wv, muk, muv = _inputs(wl, r_k, r_v, B, M, True, torch.bfloat16)
+    ck = torch.full((B, 3, 6, r_k, 64), SENTINEL, dtype=torch.bfloat16, device=DEV)
+    cv = torch.full((B, 3, 6, r_v, 64), SENTINEL, dtype=torch.bfloat16, device=DEV)
+    lla.encode(xk, xv, wk, wv, ck, cv, T=4, pos0=pos0, mu_k=muk, mu_v=muv, evict=(sink, window))
+    p = np.arange(pos0, pos0 + M)
+    slot = np.where(p < sink, p, sink + (p - sink) % window)
+    for x, w, mu, c in ((xk, wk, muk, ck), (xv, wv, muv, cv)):
+        got = f64(lla.from_paged(c))
+        assert_close(got[:, :, slot], oracle.encode_batched(f64(x), f64(mu), f64(w)), torch.bfloat16, f"ring {pos0}")
+        rest = np.setdiff1d(np.arange(384), slot)
+        assert np.all(got[:, :, rest] == SENTINEL)
