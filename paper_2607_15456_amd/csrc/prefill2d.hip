@@ -249,12 +249,12 @@ __global__ __launch_bounds__(kThreads) void recon2d_kernel(Prefill2dArgs a) {
 // reads (ds_read_b64_tr_b16) and outputs are those of the per-head
 // recon2d_kernel above.
 // ---------------------------------------------------------------------------
-template <int AXIS, int KS>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
-void recon_ph_kernel(Prefill2dArgs a, int ppw) {
-  constexpr int R = KS * 16;
-  constexpr int CPT = (R * 8 + kThreads - 1) / kThreads;  // 16-byte chunks of a page per thread
-  __shared__ __attribute__((aligned(16))) bf16_t s_c[R * kPage];
+// KS: K-steps of 16 features; BOTH: of the larger rank, and the other axis skips
+// the steps past its own rank in groups of 4.
+constexpr int kBothSteps = 20;  // largest K-step count of the launch of both axes
+template <int AXIS, int KS, bool BOTH>
+__device__ __forceinline__ void recon_ph_body(const Prefill2dArgs& a, int ppw, bf16_t* s_c) {
+  constexpr int CPT = (KS * 16 * 8 + kThreads - 1) / kThreads;  // 16-byte chunks of a page per thread
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -262,6 +262,7 @@ void recon_ph_kernel(Prefill2dArgs a, int ppw) {
   const int bh = blockIdx.y, h = bh % a.H;
   const int nvalid = a.p0 + a.M;
   const int rr = AXIS == 0 ? a.rk : a.rv;
+  const int R = BOTH ? min((rr + 63) / 64 * 64, KS * 16) : KS * 16;  // staged features (zero past rr)
   const int pg0 = blockIdx.x * ppw, pg1 = min(pg0 + ppw, a.nk / kPage);
   const bf16_t* src = static_cast<const bf16_t*>(AXIS == 0 ? a.ck : a.cv) + (size_t)bh * a.n_max * rr;
 
@@ -316,12 +317,16 @@ void recon_ph_kernel(Prefill2dArgs a, int ppw) {
     if (pg + 1 < pg1) gload(pg + 1);  // in flight during this page's products
     f32x16 acc[2] = {f32x16{0.f}, f32x16{0.f}};
 #pragma unroll
-    for (int s = 0; s < KS; ++s)
+    for (int s0 = 0; s0 < KS; s0 += 4) {
+      if (16 * s0 >= R) break;  // uniform
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        const bf16x8 c = lat_op(nt, s);
-        acc[nt] = AXIS == 0 ? mfma(as_bf16x8(ua[s]), c, acc[nt]) : mfma(c, as_bf16x8(ua[s]), acc[nt]);
-      }
+      for (int s = s0; s < (s0 + 4 < KS ? s0 + 4 : KS); ++s)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          const bf16x8 c = lat_op(nt, s);
+          acc[nt] = AXIS == 0 ? mfma(as_bf16x8(ua[s]), c, acc[nt]) : mfma(c, as_bf16x8(ua[s]), acc[nt]);
+        }
+    }
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
       const int tok0 = pg * kPage + 32 * nt;
@@ -349,6 +354,19 @@ void recon_ph_kernel(Prefill2dArgs a, int ppw) {
     }
     __syncthreads();  // the page's LDS tile is read by every wavefront before the next is stored
   }
+}
+
+// AXIS 0 or 1: one axis; 2: both in one launch (blockIdx.z).  With few pages a
+// workgroup's chain of dependent steps (latents, LDS, products, stores) is longer
+// than its share of the machine's work, so the axes overlap.
+template <int AXIS, int KS>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void recon_ph_kernel(Prefill2dArgs a, int ppw) {
+  __shared__ __attribute__((aligned(16))) bf16_t s_c[KS * 16 * kPage];
+  if (AXIS == 0 || (AXIS == 2 && blockIdx.z == 0))
+    recon_ph_body<0, KS, AXIS == 2>(a, ppw, s_c);
+  else
+    recon_ph_body<1, KS, AXIS == 2>(a, ppw, s_c);
 }
 
 // ---------------------------------------------------------------------------
@@ -1089,16 +1107,14 @@ hipError_t launch_prefill_2d(const Prefill2dArgs& a, hipStream_t stream) {
 }
 
 template <int AXIS>
-hipError_t launch_recon_ph(const Prefill2dArgs& a, int r, hipStream_t stream) {
-  // pages per workgroup: about 2048 workgroups over the (b, h) pages, 1 to 8 pages each
-  const int pages = a.nk / kPage;
-  const long total = (long)pages * a.B * a.H;
-  int ppw = (int)(total / 2048);
-  ppw = ppw < 1 ? 1 : ppw > 8 ? 8 : ppw;
-  const dim3 grid((pages + ppw - 1) / ppw, a.B * a.H);
+hipError_t launch_recon_ph(const Prefill2dArgs& a, int r, int ppw, hipStream_t stream) {
+  const dim3 grid((a.nk / kPage + ppw - 1) / ppw, a.B * a.H, AXIS == 2 ? 2 : 1);
   switch ((r + 15) / 16) {
-#define LLA_R(ks) \
-  case ks: hipLaunchKernelGGL((recon_ph_kernel<AXIS, ks>), grid, dim3(kThreads), 0, stream, a, ppw); break;
+#define LLA_R(ks)                                                                                        \
+  case ks:                                                                                               \
+    if constexpr (AXIS < 2 || ks <= kBothSteps)                                                          \
+      hipLaunchKernelGGL((recon_ph_kernel<AXIS, ks>), grid, dim3(kThreads), 0, stream, a, ppw);          \
+    break;
     LLA_R(1) LLA_R(2) LLA_R(3) LLA_R(4) LLA_R(5) LLA_R(6) LLA_R(7) LLA_R(8)
     LLA_R(9) LLA_R(10) LLA_R(11) LLA_R(12) LLA_R(13) LLA_R(14) LLA_R(15) LLA_R(16)
     LLA_R(17) LLA_R(18) LLA_R(19) LLA_R(20) LLA_R(21) LLA_R(22) LLA_R(23) LLA_R(24)
@@ -1110,9 +1126,23 @@ hipError_t launch_recon_ph(const Prefill2dArgs& a, int r, hipStream_t stream) {
 }
 
 hipError_t launch_prefill_rebuild(const Prefill2dArgs& a, hipStream_t stream) {
-  hipError_t e = launch_recon_ph<0>(a, a.rk, stream);
-  if (e != hipSuccess) return e;
-  e = launch_recon_ph<1>(a, a.rv, stream);
+  // pages per workgroup: about 2048 workgroups over the (b, h) pages, 1 to 8 pages each
+  const long total = (long)(a.nk / kPage) * a.B * a.H;
+  const int ppw = (int)max(1L, min(8L, total / 2048));
+  const int r = max(a.rk, a.rv);
+  // Both axes in one launch below 4096 pages (one workgroup per page, two rounds
+  // of the machine at most): per call, 16 heads, two launches / one, 70 tokens
+  // after 100 (192, 320) 21.2 / 15.2 us, 100 tokens (96, 160) 16.9 / 14.9, 2 x 500
+  // after 500 (120, 200) 34.5 / 30.2, 300 after 7000 (96, 160) 87.4 / 85.6.  With
+  // more pages nothing is gained, and above 320 features the kernel of both axes
+  // spills registers.
+  hipError_t e;
+  if (r <= 16 * kBothSteps && total < 4096) {
+    e = launch_recon_ph<2>(a, r, ppw, stream);
+  } else {
+    e = launch_recon_ph<0>(a, a.rk, ppw, stream);
+    if (e == hipSuccess) e = launch_recon_ph<1>(a, a.rv, ppw, stream);
+  }
   if (e != hipSuccess) return e;
   return launch_attention(a, stream);
 }

@@ -271,3 +271,17 @@ def test_bf16_prefill_other_head_widths(d):
     out = lla.prefill_attn(q, pk, pv, uk, uv, p0=7, mu_k=muk, mu_v=muv)
     torch.cuda.synchronize()
     assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, 7), torch.bfloat16, f"d_head={d}")
+
+
+@pytest.mark.parametrize("r_k,r_v", [(8, 200), (320, 40), (104, 320), (96, 160), (200, 328)])
+@pytest.mark.parametrize("B,M,p0", [(1, 1, 64), (2, 65, 3), (1, 130, 500)])
+def test_rebuild_of_both_axes(r_k, r_v, B, M, p0):
+    """Short prompts above the absorbed kernel's ranks: K and V rebuilt in one
+    launch, either axis the larger one (the other skips steps), ranks that end
+    inside a group of 64 features; (200, 328) takes two launches."""
+    log(f"prefill rebuild r=({r_k},{r_v}) B={B} M={M} p0={p0}")
+    wl = W.Workload("pf_both", 1, 3, 128, 4, B, 0, ((r_k, r_v),), torch.bfloat16)
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, B, M, p0, torch.bfloat16)
+    out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
+    torch.cuda.synchronize()
+    assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, p0), torch.bfloat16, "rebuild")
