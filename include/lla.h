@@ -244,7 +244,7 @@ lla_status lla_decode_attn_noalloc(int dtype, int out_dtype, int B, int H, int d
  *   other arguments as for lla_decode_attn.
  *
  * Requires M >= 1, p0 >= 0, p0 + M <= n_max, and the decode size limits.
- * fp32 runs an fp32 scan (one workgroup per query).  bf16 runs one of two
+ * fp32 runs in fp32 (fp32 products and sums).  bf16 runs one of two
  * kernels, each with fp32 accumulation:
  *  - r_k <= 95 and r_v <= 95 (d_head <= 128): the absorbed form of App. J,
  *    q~ = U_k^T q, s_n = q~ . c_k[n], z = sum_n p_n c_v[n], out = U_v z / l +
