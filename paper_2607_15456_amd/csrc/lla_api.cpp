@@ -604,7 +604,7 @@ lla_status lla_decode_attn_fullrope(int dtype, int out_dtype, int B, int H, int 
   a.uv = u_v;
   a.muk = mu_k;
   a.muv = mu_v;
-  a.base = base;
+  a.log2_base = std::log2(base);
   a.qscale = (float)((double)scale * kLog2e);
   a.out = out;
   a.splits = 1;
