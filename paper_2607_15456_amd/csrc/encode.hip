@@ -378,7 +378,7 @@ __global__ __launch_bounds__(256) void encode_few_kernel(EncodeArgs a, int nrc_k
 // first read.  W_down^T mu is formed on the vector unit from the staged weights.
 // Measured against one 8-wavefront workgroup of 256 x 96 per compute unit with
 // both operands in shared LDS: 2 x 3001 tokens (192, 320) with means 227 -> 130
-// us (a read of x at the copy rate is 76), 4 x 8192 (288, 480) 1131 -> 799 us
+// us (its bytes at the copy rate take 59), 4 x 8192 (288, 480) 1131 -> 799 us
 // (516 TFLOP/s), 300 tokens (96, 160) 35 -> 20, the LLA-2D stack (K = 8192) 2 x
 // 4096 tokens 152 -> 137 us (753 TFLOP/s).  LDS reads and the matrix units now
 // take about the same time.
