@@ -90,6 +90,18 @@ __device__ __forceinline__ float half_swap_sum(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// The running maximum m of a query once a block's largest score is m + mx, an
+// fp16 value (the score product subtracts it as an operand).  A wavefront may
+// meet keys far below the query's others first: m stays finite below fp16's range
+// (their weights are 0 either way), and where fp16 values are 32 apart a maximum
+// halfway is not rounded down, which would make its weight 2^16, infinity in fp16.
+__device__ __forceinline__ float raised_max(float m, float mx) {
+  const float x = m + mx;
+  float r = fmaxf((float)(_Float16)x, -65504.f);
+  if (x - r >= 16.f) r += 32.f;
+  return r;
+}
+
 // ---------------------------------------------------------------------------
 // Rebuild.  One workgroup = 128 tokens of one sequence and a run of heads (all of
 // them for a long prompt): the latent tile is staged once in LDS token-major (a token's r features contiguous) and
@@ -527,7 +539,7 @@ void flash2d_kernel(Prefill2dArgs a) {
       const bool raise = mx > kLazy || p == 0;
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
         if (raise) {
-          const float m_new = (float)(_Float16)(m_run + mx);
+          const float m_new = raised_max(m_run, mx);
           const float delta = m_new - m_run;  // exact: both are fp16 values
           const float alpha = p == 0 ? 0.f : __builtin_amdgcn_exp2f(-delta);
 #pragma unroll
@@ -724,7 +736,7 @@ void flash2d_split_kernel(Prefill2dArgs a) {
     const bool raise = mx > kLazy || (!seen && mx > neg_inf());
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
       if (raise) {
-        const float m_new = (float)(_Float16)(m_run + mx);
+        const float m_new = raised_max(m_run, mx);
         const float delta = m_new - m_run;  // exact: both are fp16 values
         const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 0.f;
 #pragma unroll
@@ -873,7 +885,6 @@ void flash2d_streams_kernel(Prefill2dArgs a) {
       for (int e = 0; e < 8; ++e) qop[s][e] = (_Float16)(x[e] * qs);
     }
   }
-  const f16x8 a_one = {(_Float16)(g == 0 ? 1.f : 0.f), 0, 0, 0, 0, 0, 0, 0};
 
   f32x16 oacc[kD / 32];
 #pragma unroll
@@ -899,6 +910,9 @@ void flash2d_streams_kernel(Prefill2dArgs a) {
         for (int kt = 0; kt < NT; ++kt)
           kop[s][kt] = *reinterpret_cast<const uint4*>(sk + 32 * kt * kD + (((2 * s + g) ^ (col & 15)) << 3));
       __builtin_amdgcn_sched_barrier(0);
+      int gr = g;
+      asm volatile("" : "+v"(gr));  // a_one formed here, not held over the rounds (it would spill)
+      const f16x8 a_one = {(_Float16)(gr == 0 ? 1.f : 0.f), 0, 0, 0, 0, 0, 0, 0};
       const f16x8 b_m = {(_Float16)(g == 0 ? -m_run : 0.f), 0, 0, 0, 0, 0, 0, 0};
       f32x16 sc[NT];
 #pragma unroll
@@ -939,7 +953,7 @@ void flash2d_streams_kernel(Prefill2dArgs a) {
       const bool raise = mx > kLazy || (!seen && mx > neg_inf());
       if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
         if (raise) {
-          const float m_new = (float)(_Float16)(m_run + mx);
+          const float m_new = raised_max(m_run, mx);
           const float delta = m_new - m_run;  // exact: both are fp16 values
           const float alpha = seen ? __builtin_amdgcn_exp2f(-delta) : 0.f;
 #pragma unroll

@@ -236,6 +236,38 @@ def test_bf16_prefill_key_streams(B, M, p0, qmul, kramp, means):
     assert_close(o, ref, torch.bfloat16, "key streams")
 
 
+@pytest.mark.parametrize("B,M,p0", [(1, 33, 1070), (1, 300, 2000), (1, 1000, 1031), (4, 270, 1500), (1, 3970, 5),
+                                    (4, 1900, 0)])
+@pytest.mark.parametrize("low", [-170.0, -86.0])
+def test_bf16_prefill_far_below(B, M, p0, low):
+    """Runs of keys whose base-2 logits lie below the range of the fp16 running
+    maximum (about -83,000), or at its coarsest (about -42,000, where it is a
+    multiple of 32), beside ordinary ones: weight 0, and the query's other keys
+    count as ever, whichever workgroup or wavefront meets such a run first."""
+    wl = W.Workload("pf_far", 1, 16, 128, 4, B, 0, ((96, 160),), torch.bfloat16)
+    log(f"far below B={B} M={M} p0={p0} low={low}")
+    q, ck, cv, uk, uv, _, _, _, _ = _case(wl, 96, 160, B, M, p0, torch.bfloat16, means=False)
+    N = p0 + M
+    n = torch.arange(N, device=DEV)
+    far = (n // 64 == 1) | ((n // 256) % 2 == 1)
+    # feature 0 adds 30 * 128 * low * log2(e) / sqrt(128) to a far key's logit; the other features are small
+    # enough for the usual tolerance at queries near 30
+    uk = uk * 0.02
+    uk[:, :, 0] = 1.0
+    ck[:, :, :, 0] = torch.where(far, low, 0.0).to(ck.dtype)
+    q = (30.0 + q.float()).to(q.dtype)
+    n_max = (N + 63) // 64 * 64
+    pk, pv = _paged(ck, n_max, True), _paged(cv, n_max, True)
+    out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(out).all())
+    rows = sorted({r for e in (0, 32, 64, 128, 256, 512, M - M % 32, M - 1) for r in (e - 1, e, e + 1) if 0 <= r < M})
+    heads = [0, 15]
+    ref = np.stack([_rows_absorbed(q[:, [h]], ck[:, [h]], cv[:, [h]], uk[[h]], uv[[h]], None, None, p0,
+                                   rows=rows)[:, 0] for h in heads], axis=1)
+    assert_close(f64(out[:, heads][:, :, rows]), ref, torch.bfloat16, "far below")
+
+
 @pytest.mark.slow
 @pytest.mark.parametrize("r_k,r_v", [(96, 160), (288, 480)])
 def test_full_prefill_tier(r_k, r_v):
