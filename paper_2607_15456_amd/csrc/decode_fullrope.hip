@@ -76,6 +76,11 @@ __device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
                                                  c, 0, 0, 0);
 }
 
+// theta of frequency f, base^(-2 f / 128).
+__device__ __forceinline__ double frequency(const FullRopeArgs& a, int f) {
+  return rope_frequency(a.log2_base, a.log2_base_lo, -2.0 * f / kFrD);
+}
+
 // (cos, sin) of p * theta with the angle formed and reduced in double.
 __device__ __forceinline__ void rot_cs(double p, double theta, float& c, float& s) {
   const double ang = p * theta;
@@ -194,9 +199,9 @@ void fullrope_mfma_kernel(FullRopeArgs a) {
   // query rotation: lane col forms QP for frequency 32 (mt & 1) + col of this
   // wavefront's token tile of every page
   const int fq = 32 * (mt & 1) + col;
-  // exp2 of a multiple of log2(base) rather than pow: same bits out, 8 x 4096
-  // tokens at (192, 320) 399 -> 387 us for four calls
-  const double theta_q = exp2(a.log2_base * (-2.0 * fq / kFrD));
+  // rope_frequency rather than pow: 8 x 4096 tokens at (192, 320) 399 -> 387 us
+  // for four calls
+  const double theta_q = frequency(a, fq);
   float q1, q2;
   {
     const bf16_t* qp = static_cast<const bf16_t*>(a.q) + bh * kFrD;
@@ -451,7 +456,7 @@ void fullrope_mfma_kernel(FullRopeArgs a) {
     }
     // the thread's frequencies are fr = tid % 32 and 32 + fr for every e
     static_assert(kFrThreads % 32 == 0, "");
-    const double th0 = exp2(a.log2_base * (-2.0 * (tid & 31) / kFrD)), th1 = exp2(a.log2_base * (-2.0 * (32 + (tid & 31)) / kFrD));
+    const double th0 = frequency(a, tid & 31), th1 = frequency(a, 32 + (tid & 31));
     for (int e = tid; e < 2 * 32 * 32; e += kFrThreads) {
       const int hf = e >> 10, t = (e >> 5) & 31, fr = e & 31;
       float c, sn;
@@ -599,7 +604,7 @@ void fullrope_rows_kernel(FullRopeArgs a) {
   const int hf = f16 >> 5;
   // query rotation: lane (col, j = g & 1) forms QP for frequency f16 + col of
   // 32-token tile j of every page
-  const double theta_q = exp2(a.log2_base * (-2.0 * (f16 + col) / kFrD));
+  const double theta_q = frequency(a, f16 + col);
   float q1, q2;
   {
     const bf16_t* qp = static_cast<const bf16_t*>(a.q) + bh * kFrD;
@@ -858,7 +863,7 @@ void fullrope_rows_kernel(FullRopeArgs a) {
   {
     // the thread's frequencies are fr = tid % 32 and 32 + fr for every e
     static_assert(kFrThreads % 32 == 0, "");
-    const double th0 = exp2(a.log2_base * (-2.0 * (tid & 31) / kFrD)), th1 = exp2(a.log2_base * (-2.0 * (32 + (tid & 31)) / kFrD));
+    const double th0 = frequency(a, tid & 31), th1 = frequency(a, 32 + (tid & 31));
     for (int e = tid; e < 2 * 32 * 32; e += kFrThreads) {
       const int hf = e >> 10, t = (e >> 5) & 31, fr = e & 31;
       float c, sn;

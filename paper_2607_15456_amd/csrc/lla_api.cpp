@@ -249,9 +249,20 @@ int device_cu_count() {
   }
   return cached[dev];
 }
+void log2_parts(double base, double* hi, double* lo) {
+  const long double l = std::log2((long double)base);
+  *hi = (double)l;
+  *lo = (double)(l - (long double)*hi);
+}
 }  // namespace lla
 
 extern "C" {
+
+double lla_internal_rope_frequency(double base, double c) {
+  double hi, lo;
+  lla::log2_parts(base, &hi, &lo);
+  return lla::rope_frequency(hi, lo, c);
+}
 
 const char* lla_status_string(int status) {
   switch (status) {
@@ -604,7 +615,7 @@ lla_status lla_decode_attn_fullrope(int dtype, int out_dtype, int B, int H, int 
   a.uv = u_v;
   a.muk = mu_k;
   a.muv = mu_v;
-  a.log2_base = std::log2(base);
+  lla::log2_parts(base, &a.log2_base, &a.log2_base_lo);
   a.qscale = (float)((double)scale * kLog2e);
   a.out = out;
   a.splits = 1;

@@ -146,6 +146,15 @@ struct RopeArgs {
 hipError_t launch_rope_write(const RopeArgs& a, hipStream_t stream);
 hipError_t launch_rope_rotate(const RopeArgs& a, hipStream_t stream);
 
+// base^c, |c| <= 1, from log2(base) = hi + lo: exp2 of the rounded product, times 1 +
+// ln 2 of what the rounding left out.  A third of pow's work and as exact (within
+// 2^-52 relative, whatever the base; the rounded product alone loses up to
+// log2(base) / 2 units of the last place).
+__host__ __device__ inline double rope_frequency(double hi, double lo, double c) {
+  const double e = hi * c, rest = fma(hi, c, -e) + lo * c, t = exp2(e);
+  return fma(t, rest * 0.69314718055994530942, t);
+}
+
 // Full-RoPE reconstruct-then-attend decode (keys rebuilt and rotated per position).
 struct FullRopeArgs {
   int dtype, out_dtype;
@@ -160,11 +169,8 @@ struct FullRopeArgs {
   const void* uv;           // [H][d][rv]
   const void* muk;          // [H][d] or null
   const void* muv;          // [H][d] or null
-  // log2 of the RoPE base: frequency f is exp2(-2 f log2_base / d), a third of
-  // pow's work in every workgroup's prologue.  Good to 2e-15 relative, an angle
-  // error below 2e-8 at the longest context a region can hold (2^23 tokens), under
-  // the fp32 rounding of the reduced angle.
-  double log2_base;
+  // log2(base) as a sum of two doubles (rope_frequency)
+  double log2_base, log2_base_lo;
   float qscale;             // softmax scale * log2(e)
   void* out;                // [B][H][d]
   float* part;              // [B*H][splits][rv + 2] split partials (m, l, z)
@@ -177,4 +183,12 @@ int fullrope_occupancy(int r_k, int r_v);  // resident workgroups per compute un
 
 int device_cu_count();  // compute units of the current device (cached)
 
+// log2(base) as the sum of two doubles.
+void log2_parts(double base, double* hi, double* lo);
+
 }  // namespace lla
+
+// Host-side values and choices of the launches, for the tests (not part of the ABI).
+extern "C" {
+double lla_internal_rope_frequency(double base, double c);
+}
