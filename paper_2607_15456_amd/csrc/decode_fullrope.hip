@@ -978,7 +978,9 @@ __global__ __launch_bounds__(256) void fullrope_plain_kernel(FullRopeArgs a) {
   const size_t bh = (size_t)b * a.H + h;
   const T* q = static_cast<const T*>(a.q) + bh * d;
   for (int i = tid; i < d; i += 256) s_q[i] = Elem<T>::get(q, i) * a.qscale;
-  for (int f = tid; f < half; f += 256) s_theta[f] = exp2(a.log2_base * (-2.0 * f / d));
+  // pow: with exp2 of multiples of log2(base) the whole kernel compiles to code
+  // that takes 4 to 9% longer (fp32 (96, 160), 4 heads, 868 tokens 3079 -> 3357 us)
+  for (int f = tid; f < half; f += 256) s_theta[f] = pow(a.base, -2.0 * f / d);
   const T* ck = static_cast<const T*>(a.ck) + bh * (size_t)a.n_max * rk;
   const T* cv = static_cast<const T*>(a.cv) + bh * (size_t)a.n_max * rv;
   const T* uk = static_cast<const T*>(a.uk) + (size_t)h * d * rk;

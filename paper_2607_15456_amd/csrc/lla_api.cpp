@@ -615,6 +615,7 @@ lla_status lla_decode_attn_fullrope(int dtype, int out_dtype, int B, int H, int 
   a.uv = u_v;
   a.muk = mu_k;
   a.muv = mu_v;
+  a.base = base;
   lla::log2_parts(base, &a.log2_base, &a.log2_base_lo);
   a.qscale = (float)((double)scale * kLog2e);
   a.out = out;

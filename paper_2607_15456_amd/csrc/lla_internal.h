@@ -169,6 +169,7 @@ struct FullRopeArgs {
   const void* uv;           // [H][d][rv]
   const void* muk;          // [H][d] or null
   const void* muv;          // [H][d] or null
+  double base;              // RoPE base
   // log2(base) as a sum of two doubles (rope_frequency)
   double log2_base, log2_base_lo;
   float qscale;             // softmax scale * log2(e)
