@@ -552,8 +552,10 @@ __device__ __forceinline__ void encode_gemm_body(const EncodeArgs& a, int tfirst
       // of a 32-token tile, so registers 4i .. 4i + 3 are 4 consecutive tokens
       // of one feature row.  Each wavefront turns a row tile through its own
       // LDS tile [row][token]; runs of 4 lanes then store a row's tokens 16
-      // bytes each when their slots are 8 consecutive ones of one sequence from
-      // a multiple of 8, else one element at a time.
+      // bytes each where their slots are 8 consecutive ones of one sequence from
+      // a multiple of 8.  Other tokens are stored by a lane each, two rows at a
+      // time (a wavefront's stores are then two runs of consecutive slots; eight
+      // tokens by one lane in turn touched 16 rows per store).
       bf16_t* tile = s.tile[wave];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -568,24 +570,35 @@ __device__ __forceinline__ void encode_gemm_body(const EncodeArgs& a, int tfirst
             *reinterpret_cast<uint2*>(&tile[col * 40 + 8 * i + 4 * g]) = make_uint2(v[0] | (v[1] << 16), v[2] | (v[3] << 16));
           }
           wave_sync();
+          const int tt = tw + 32 * u;
+          // whether the 8 tokens from t are 8 consecutive slots from a multiple of 8
+          auto whole = [&](int t, int& b, int& p) {
+            b = t / a.M;
+            const int m0 = t - b * a.M;
+            p = ring_slot(a.pos0 + m0, a.sink, a.window);
+            return t >= tlo && t + 7 < thi && m0 + 7 < a.M && (p & 7) == 0 &&
+                   ring_slot(a.pos0 + m0 + 7, a.sink, a.window) == p + 7;
+          };
+          const int grp = lane & 3;
+          int b, p;
+          if (whole(tt + 8 * grp, b, p)) {
 #pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            const int rl = (lane >> 2) + 16 * k, grp = lane & 3, row = rw + 32 * rt + rl;
-            const int t = tw + 32 * u + 8 * grp;  // first token of the piece
-            if (row >= r || t + 7 < tlo || t >= thi) continue;
-            const int b = t / a.M, m0 = t - b * a.M;
-            const int p = ring_slot(a.pos0 + m0, a.sink, a.window);
-            if (t >= tlo && t + 7 < thi && m0 + 7 < a.M && (p & 7) == 0 &&
-                ring_slot(a.pos0 + m0 + 7, a.sink, a.window) == p + 7) {
-              *reinterpret_cast<uint4*>(&cout[cache_index(b, hh, H, a.n_max, r, p, row)]) =
-                  *reinterpret_cast<const uint4*>(&tile[rl * 40 + 8 * grp]);
-            } else {
-#pragma unroll 1
-              for (int te = max(t, tlo); te < min(t + 8, thi); ++te) {
-                const int be = te / a.M, pos = ring_slot(a.pos0 + (te - be * a.M), a.sink, a.window);
-                cout[cache_index(be, hh, H, a.n_max, r, pos, row)] = tile[rl * 40 + 8 * grp + te - t];
-              }
+            for (int k = 0; k < 2; ++k) {
+              const int rl = (lane >> 2) + 16 * k, row = rw + 32 * rt + rl;
+              if (row < r)
+                *reinterpret_cast<uint4*>(&cout[cache_index(b, hh, H, a.n_max, r, p, row)]) =
+                    *reinterpret_cast<const uint4*>(&tile[rl * 40 + 8 * grp]);
             }
+          }
+          const int te = tt + col;
+          if (te >= tlo && te < thi && !whole(tt + (col & ~7), b, p)) {
+            b = te / a.M;
+            p = ring_slot(a.pos0 + (te - b * a.M), a.sink, a.window);
+            const int row0 = rw + 32 * rt + g;
+            bf16_t* dst = &cout[cache_index(b, hh, H, a.n_max, r, p, row0)];
+#pragma unroll 4
+            for (int i = 0; i < 16; ++i)
+              if (row0 + 2 * i < r) dst[2 * i * kPage] = tile[(2 * i + g) * 40 + col];
           }
           wave_sync();
         }

@@ -224,7 +224,7 @@ def test_fp32_tiles(r_k, r_v, M, pos0, d_head):
 
 @pytest.mark.parametrize("r_k,r_v", [(33, 65), (160, 97), (96, 320), (36, 60)])
 @pytest.mark.parametrize("B,M,pos0,T,d_head", [(1, 192, 0, 4, 128), (3, 171, 5, 4, 128), (2, 601, 61, 2, 96),
-                                               (40, 13, 7, 1, 64), (2, 1500, 3, 4, 128)])
+                                               (40, 13, 7, 1, 64), (90, 3, 5, 1, 64), (2, 1500, 3, 4, 128)])
 @pytest.mark.parametrize("means", [False, True])
 def test_gemm_tiles(r_k, r_v, B, M, pos0, T, d_head, means):
     """The GEMM write at the edges of its blocks: row blocks of 3, 2 and 1
