@@ -15,6 +15,7 @@
 //
 // fp32: the same product on the fp32 matrix instructions, 32 x 32 tiles.
 
+#include <algorithm>
 #include <type_traits>
 
 #include "lla_device.h"
@@ -611,9 +612,9 @@ __device__ __forceinline__ void encode_gemm_body(const EncodeArgs& a, int tfirst
   };
 
   // Chunk q's weights are in LDS buffer q % 2, its x in the wavefront's region,
-  // chunks q + 1 .. q + NR of x in registers (q + 1 in slot q % NR; nkc is a
-  // multiple of NR whenever a workgroup takes more than one head).  W chunk
-  // q + 1 is stored to the buffer that chunk q - 1 left, after chunk q's
+  // chunks q + 1 .. q + NR of x in registers (q + 1 in slot q % NR; with
+  // NR = 2 a workgroup takes one head, so any number of chunks will do).  W
+  // chunk q + 1 is stored to the buffer that chunk q - 1 left, after chunk q's
   // products; x chunk q + 1 after them in the wavefront's own order.
   wload();
   xload(x[NR - 1], 0);
@@ -792,16 +793,72 @@ __global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a, int nrc_k
   }
 }
 
-}  // namespace
+// Launch of a bf16 GEMM write with 32 XT tokens per wavefront.
+template <int XT>
+struct GemmGrid {
+  int nrb_k, nrb;  // row blocks of axis k, of both axes
+  int nsb, ntb;    // token blocks per sequence (0: of the flattened tokens), in all
+  int hpw;         // heads per workgroup
+  int rounds;      // workgroups that one slot of the busiest XCD takes in turn (two slots per compute unit)
+  explicit GemmGrid(const EncodeArgs& a) {
+    const int TT = a.B * a.M, q = 128 * XT;
+    nrb_k = (a.r[0] + kGRow - 1) / kGRow;
+    nrb = nrb_k + (a.r[1] + kGRow - 1) / kGRow;
+    // Blocks cut per sequence unless that adds rounds of the 8 XCDs (3 x 600
+    // tokens (240, 400) with means: 9 blocks for 8 took 88 us, 60 in one round).
+    nsb = (a.M + (a.pos0 & 7) + q - 1) / q;
+    ntb = (TT + q - 1) / q;
+    if (((int64_t)nsb * a.B + 7) / 8 <= (ntb + 7) / 8 * 17 / 16)
+      ntb = nsb * a.B;
+    else
+      nsb = 0;
+    // With 64 tokens per wavefront as many heads as keep at least 2048
+    // workgroups (four rounds of the machine), so short stacks (per-head
+    // writes) do not pay the pipeline fill per head; 32 are for few workgroups.
+    hpw = 1;
+    if (XT == 2) hpw = (int)std::min<int64_t>(a.H, std::max<int64_t>(1, (int64_t)a.H * nrb * ntb / 2048));
+    const int64_t per_xcd = (int64_t)((ntb + 7) / 8) * nrb * a.H, slots = std::max(1, device_cu_count() / 4);
+    rounds = (int)((per_xcd + slots - 1) / slots);
+  }
+};
 
-// Heads per workgroup: as many as keep at least 2048 workgroups (four rounds of
-// the machine), so short stacks (per-head writes) do not pay the pipeline fill
-// per head.
-static int gemm_heads_per_wg(int H, int blocks, int nkc, int ring) {
-  if (nkc % ring) return 1;  // a run of heads needs every head to start on the same register set
-  const int hpw = (int)((int64_t)H * blocks / 2048);
-  return hpw < 1 ? 1 : hpw > H ? H : hpw;
+// Many tokens: the GEMM from 256 tokens (512 at ranks up to 64, whose
+// weights the 32-token kernel re-reads cheaply; 192 above 64 over a per-head
+// stack), measured GEMM / 32-token kernel at K = 512: 200 tokens (96, 160)
+// 18.0 / 19.4 us, (288, 480) 29.5 / 41.5; 130 tokens 16.1 / 13.5; (36, 60)
+// 300 tokens 12.7 / 12.0, 3000 tokens 26.4 / 75.7.
+bool gemm_ok(const EncodeArgs& a) {
+  const int TT = a.B * a.M, rmax = a.r[0] > a.r[1] ? a.r[0] : a.r[1];
+  return a.K % kGKC == 0 && TT >= (a.K >= 2048 ? 256 : rmax > 64 ? 192 : 512);
 }
+
+// 64 tokens per wavefront where that leaves two workgroups per compute
+// unit to take (2 x 3001 tokens (192, 320) 130 us, 32 per wavefront 158),
+// else 32 (300 tokens (96, 160) 20 us, 64 per wavefront 31)
+bool gemm_wide(const EncodeArgs& a) {
+  return (int64_t)((a.B * a.M + 255) / 256) * GemmGrid<2>(a).nrb * a.H >= 2 * device_cu_count();
+}
+
+// The kernel of a bf16 write.
+enum Route { kFew, kStream, kTok32, kGemm1, kGemm2 };
+Route bf16_route(const EncodeArgs& a) {
+  const int TT = a.B * a.M, blocks = (TT + kEncTok - 1) / kEncTok, rmax = a.r[0] > a.r[1] ? a.r[0] : a.r[1];
+  if (TT <= 64) return kFew;  // a decode step's writes: weights read once, one round of loads
+  // prefill-sized write at small ranks: resident weights, streamed tokens
+  if (blocks >= 256 && rmax <= 64 && (a.K == 512 || a.K == 256)) return kStream;
+  if (gemm_ok(a)) return gemm_wide(a) ? kGemm2 : kGemm1;
+  return kTok32;
+}
+
+template <int XT>
+hipError_t launch_gemm(const EncodeArgs& a, hipStream_t stream) {
+  const GemmGrid<XT> g(a);
+  hipLaunchKernelGGL((encode_gemm_kernel<XT>), dim3(g.nrb * ((g.ntb + 7) / 8 * 8), (a.H + g.hpw - 1) / g.hpw),
+                     dim3(kGThreads), 0, stream, a, g.nrb_k, g.nrb, g.ntb, g.nsb, g.hpw);
+  return hipGetLastError();
+}
+
+}  // namespace
 
 int encode_ksplit(int TT, int K) {
   if (TT > 64 || K < 2048) return 1;
@@ -819,21 +876,22 @@ size_t encode_ws_bytes(int B, int M, int H, int K, int r_k, int r_v) {
 hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
   const int TT = a.B * a.M;
   const int rmax = a.r[0] > a.r[1] ? a.r[0] : a.r[1];
-  if (a.dtype == LLA_BF16) {
-    // Many tokens: a workgroup streams all heads of its 32 tokens (one
-    // contiguous region of x).  Fewer tokens: one head and two row tiles per
-    // workgroup, so the weights spread over the machine.
-    const int blocks = (TT + kEncTok - 1) / kEncTok;
-    if (TT <= 64) {  // a decode step's writes: weights read once, one round of loads
-      const int nrc_k = (a.r[0] + 31) / 32, nrc_v = (a.r[1] + 31) / 32;
+  const int nrc_k = (a.r[0] + 31) / 32, nrc_v = (a.r[1] + 31) / 32;
+  if (a.dtype == LLA_F32) {
+    dim3 grid((TT + 31) / 32 * (nrc_k + nrc_v), a.H);
+    hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, a, nrc_k, nrc_k + nrc_v);
+    return hipGetLastError();
+  }
+  const int blocks = (TT + kEncTok - 1) / kEncTok;
+  switch (bf16_route(a)) {
+    case kFew: {
       dim3 grid(blocks, nrc_k + nrc_v, a.H * a.ksplit);
       hipLaunchKernelGGL(encode_few_kernel, grid, dim3(256), 0, stream, a, nrc_k);
       if (a.ksplit > 1)
         hipLaunchKernelGGL(encode_reduce_kernel, dim3(blocks, nrc_k + nrc_v, a.H), dim3(256), 0, stream, a, nrc_k);
       return hipGetLastError();
     }
-    if (blocks >= 256 && rmax <= 64 && (a.K == 512 || a.K == 256)) {
-      // prefill-sized write: resident weights, streamed tokens; ~2 workgroups per CU
+    case kStream: {  // ~2 workgroups per CU
       const int per_head = 2 * a.H;
       int wgx = (2 * device_cu_count() + per_head - 1) / per_head;
       if (wgx > blocks) wgx = blocks;
@@ -845,49 +903,45 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
         hipLaunchKernelGGL((encode_stream_kernel<8>), grid, dim3(256), 0, stream, a, bpw);
       return hipGetLastError();
     }
-    // Many tokens: the GEMM from 256 tokens (512 at ranks up to 64, whose
-    // weights the 32-token kernel re-reads cheaply; 192 above 64 over a per-head
-    // stack), measured GEMM / 32-token kernel at K = 512: 200 tokens (96, 160)
-    // 18.0 / 19.4 us, (288, 480) 29.5 / 41.5; 130 tokens 16.1 / 13.5; (36, 60)
-    // 300 tokens 12.7 / 12.0, 3000 tokens 26.4 / 75.7.
-    const int gemm_from = a.K >= 2048 ? 256 : rmax > 64 ? 192 : 512;
-    if (TT >= gemm_from && a.K % kGKC == 0) {
-      const int nrb_k = (a.r[0] + kGRow - 1) / kGRow, nrb = nrb_k + (a.r[1] + kGRow - 1) / kGRow;
-      auto launch = [&](auto xt) {
-        constexpr int XT = decltype(xt)::value;
-        // blocks cut per sequence unless that fills them badly (short sequences)
-        int nsb = (a.M + (a.pos0 & 7) + 128 * XT - 1) / (128 * XT), ntb = (TT + 128 * XT - 1) / (128 * XT);
-        if ((int64_t)nsb * a.B <= ntb + ntb / 8 + 1)
-          ntb = nsb * a.B;
-        else
-          nsb = 0;
-        const int ntb8 = (ntb + 7) / 8 * 8;
-        const int hpw = gemm_heads_per_wg(a.H, nrb * ntb, a.K / kGKC, kGRing<XT>);
-        hipLaunchKernelGGL((encode_gemm_kernel<XT>), dim3(nrb * ntb8, (a.H + hpw - 1) / hpw), dim3(kGThreads), 0,
-                           stream, a, nrb_k, nrb, ntb, nsb, hpw);
-      };
-      // 64 tokens per wavefront where that leaves two workgroups per compute
-      // unit to take (2 x 3001 tokens (192, 320) 130 us, 32 per wavefront 158),
-      // else 32 (300 tokens (96, 160) 20 us, 64 per wavefront 31)
-      const bool wide = (int64_t)((TT + 255) / 256) * nrb * a.H >= 2 * device_cu_count();
-      if (wide)
-        launch(std::integral_constant<int, 2>{});
-      else
-        launch(std::integral_constant<int, 1>{});
-      return hipGetLastError();
-    }
-    const int heads_per_wg = blocks >= 256 ? a.H : 1;
-    const int rtmax = (rmax + 15) / 16;
-    const int rt_per_wg = blocks >= 256 ? (rtmax < 8 ? rtmax : 8) : 2;
-    const int nrc = (rtmax + rt_per_wg - 1) / rt_per_wg;
-    dim3 grid(blocks, (a.H + heads_per_wg - 1) / heads_per_wg, 2 * nrc);
-    hipLaunchKernelGGL(encode_bf16_kernel, grid, dim3(256), 0, stream, a, heads_per_wg, rt_per_wg, nrc);
-  } else {
-    const int nrc_k = (a.r[0] + 31) / 32, nrc = nrc_k + (a.r[1] + 31) / 32;
-    dim3 grid((TT + 31) / 32 * nrc, a.H);
-    hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, a, nrc_k, nrc);
+    case kGemm1: return launch_gemm<1>(a, stream);
+    case kGemm2: return launch_gemm<2>(a, stream);
+    case kTok32: break;
   }
+  // One head and two row tiles per workgroup, so that the weights spread over
+  // the machine; of 8192 tokens and more (few heads, or K an odd multiple of 32)
+  // all heads of its 32 tokens, one contiguous region of x.
+  const int heads_per_wg = blocks >= 256 ? a.H : 1;
+  const int rtmax = (rmax + 15) / 16;
+  const int rt_per_wg = blocks >= 256 ? (rtmax < 8 ? rtmax : 8) : 2;
+  const int nrc = (rtmax + rt_per_wg - 1) / rt_per_wg;
+  dim3 grid(blocks, (a.H + heads_per_wg - 1) / heads_per_wg, 2 * nrc);
+  hipLaunchKernelGGL(encode_bf16_kernel, grid, dim3(256), 0, stream, a, heads_per_wg, rt_per_wg, nrc);
   return hipGetLastError();
 }
 
 }  // namespace lla
+
+// Kernel of a bf16 write (enum Route), and of a GEMM write its heads per
+// workgroup, token blocks and rounds.
+extern "C" int lla_internal_encode_route(int B, int M, int H, int K, int r_k, int r_v, int pos0, int* heads,
+                                         int* blocks, int* rounds) {
+  lla::EncodeArgs a{};
+  a.dtype = LLA_BF16;
+  a.B = B;
+  a.M = M;
+  a.H = H;
+  a.K = K;
+  a.r[0] = r_k;
+  a.r[1] = r_v;
+  a.pos0 = pos0;
+  const lla::Route route = lla::bf16_route(a);
+  *heads = *blocks = *rounds = 0;
+  auto fill = [&](const auto& g) {
+    *heads = g.hpw;
+    *blocks = g.ntb;
+    *rounds = g.rounds;
+  };
+  if (route == lla::kGemm1) fill(lla::GemmGrid<1>(a));
+  if (route == lla::kGemm2) fill(lla::GemmGrid<2>(a));
+  return route;
+}

@@ -192,4 +192,6 @@ void log2_parts(double base, double* hi, double* lo);
 // Host-side values and choices of the launches, for the tests (not part of the ABI).
 extern "C" {
 double lla_internal_rope_frequency(double base, double c);
+int lla_internal_encode_route(int B, int M, int H, int K, int r_k, int r_v, int pos0, int* heads, int* blocks,
+                              int* rounds);
 }
