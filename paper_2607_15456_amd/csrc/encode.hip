@@ -822,22 +822,29 @@ struct GemmGrid {
   }
 };
 
-// Many tokens: the GEMM from 256 tokens (512 at ranks up to 64, whose
-// weights the 32-token kernel re-reads cheaply; 192 above 64 over a per-head
-// stack), measured GEMM / 32-token kernel at K = 512: 200 tokens (96, 160)
-// 18.0 / 19.4 us, (288, 480) 29.5 / 41.5; 130 tokens 16.1 / 13.5; (36, 60)
-// 300 tokens 12.7 / 12.0, 3000 tokens 26.4 / 75.7.
+// Whether a bf16 write of more than 64 tokens runs the GEMM rather than the
+// 32-token kernel.  A GEMM workgroup takes longer and does more, so it pays where
+// the 32-token kernel's workgroups (tokens / 32 x heads x row chunks of both
+// axes) come in several rounds: from about 900 at K = 512, more the shorter K is.
+// The line was drawn, and checked, over 3000 writes of 1 to 32 heads, K 64 to 2048,
+// ranks 1 to 512 and 65 to 40,000 tokens: the kernel turned down is faster by more
+// than 3% in one of 200, and nowhere with 16 heads and K = 512.  32-token kernel / GEMM: 300 tokens of 16 heads (96, 160) at K = 512 24.4 / 20.1 us, of 4 heads
+// (203 tokens) 8.4 / 14.6; (36, 60) 3000 tokens of 16 heads 75.7 / 26.4, 1532 of 2
+// heads 10.2 / 13.6.  Below 256 tokens its blocks are largely padding (195
+// tokens (192, 320) 24.6 / 28.0, 200 (288, 480) 41.5 / 29.5), the more so for
+// short sequences (32 of 7, 32 heads, K = 192 33.8 / 38.5).  Stacks of 2048
+// values and more (LLA-2D) gain from 256 tokens.
 bool gemm_ok(const EncodeArgs& a) {
   const int TT = a.B * a.M, rmax = a.r[0] > a.r[1] ? a.r[0] : a.r[1];
-  return a.K % kGKC == 0 && TT >= (a.K >= 2048 ? 256 : rmax > 64 ? 192 : 512);
+  if (TT < 192 || a.K % kGKC) return false;
+  const int64_t work = (int64_t)((TT + kEncTok - 1) / kEncTok) * a.H * 2 * ((rmax + 31) / 32) * (a.K + 512);
+  if (TT < 256) return a.K < 2048 && rmax > 64 && a.M >= 64 && work > 3 << 20;
+  return a.K >= 2048 || work > 900 << 10;
 }
 
-// 64 tokens per wavefront where that leaves two workgroups per compute
-// unit to take (2 x 3001 tokens (192, 320) 130 us, 32 per wavefront 158),
-// else 32 (300 tokens (96, 160) 20 us, 64 per wavefront 31)
-bool gemm_wide(const EncodeArgs& a) {
-  return (int64_t)((a.B * a.M + 255) / 256) * GemmGrid<2>(a).nrb * a.H >= 2 * device_cu_count();
-}
+// 64 tokens per wavefront where 32 take more than 1.7 times the rounds (a
+// workgroup of 64 takes 1.7 times as long as one of 32), else 32.
+bool gemm_wide(const EncodeArgs& a) { return 17 * (int64_t)GemmGrid<2>(a).rounds < 10 * (int64_t)GemmGrid<1>(a).rounds; }
 
 // The kernel of a bf16 write.
 enum Route { kFew, kStream, kTok32, kGemm1, kGemm2 };

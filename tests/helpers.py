@@ -1,5 +1,6 @@
 """Shared helpers of the GPU parity tests."""
 
+import ctypes
 import sys
 
 import numpy as np
@@ -70,3 +71,15 @@ def assert_units_close(got, ref, what=""):
     log(f"  {what}: {g2.shape[0]} units, worst max_abs={max_abs.max():.3e} "
         f"worst rel_l2={rel.max():.3e} (unit {np.unravel_index(worst, got.shape[:-1])})")
     assert max_abs.max() <= BF16_MAX_ABS and rel.max() <= BF16_REL_L2, (what, max_abs.max(), rel.max())
+
+
+# Kernels of a bf16 cache write, as the library's host-side query numbers them.
+FEW, STREAM, TOK32, GEMM1, GEMM2 = range(5)
+
+
+def encode_route(lib, B, M, H, K, r_k, r_v, pos0=0):
+    """(kernel, heads per workgroup, token blocks, rounds) that the library
+    chooses for a bf16 write."""
+    out = [ctypes.c_int() for _ in range(3)]
+    return (lib.lla_internal_encode_route(B, M, H, K, r_k, r_v, pos0, *map(ctypes.byref, out)),
+            *(o.value for o in out))

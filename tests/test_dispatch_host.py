@@ -7,6 +7,7 @@ import decimal
 import pytest
 
 from paper_2607_15456_amd import lla
+from tests.helpers import FEW, GEMM1, GEMM2, STREAM, TOK32, encode_route
 
 
 @pytest.fixture(scope="module")
@@ -31,16 +32,6 @@ def test_rope_frequency(host, base):
             assert err <= decimal.Decimal(2) ** -52, (f, float(err))
 
 
-FEW, STREAM, TOK32, GEMM1, GEMM2 = range(5)
-
-
-def encode_route(host, B, M, H, K, r_k, r_v, pos0=0):
-    """(kernel, heads per workgroup, token blocks, rounds) of a bf16 write."""
-    out = [ctypes.c_int() for _ in range(3)]
-    return (host.lla_internal_encode_route(B, M, H, K, r_k, r_v, pos0, *map(ctypes.byref, out)),
-            *(o.value for o in out))
-
-
 @pytest.mark.parametrize("B,M,pos0", [(1, 4096, 0), (2, 3001, 0), (3, 600, 0), (3, 600, 7), (5, 500, 3), (4, 8192, 1),
                                       (7, 300, 0), (64, 257, 5), (17, 513, 0)])
 def test_gemm_token_blocks(host, B, M, pos0):
@@ -55,3 +46,29 @@ def test_gemm_token_blocks(host, B, M, pos0):
     assert rounds <= least + least // 16
     if B == 1 and pos0 == 0:
         assert blocks == flat
+
+
+@pytest.mark.parametrize("B,M,H,K,r_k,r_v,route", [
+    # few workgroups: the 32-token kernel (us, 32-token / GEMM)
+    (1, 203, 4, 512, 96, 160, TOK32),      # 8.4 / 14.6
+    (1, 195, 16, 512, 192, 320, TOK32),    # 24.6 / 28.0
+    (1, 1259, 1, 320, 36, 60, TOK32),      # 5.9 / 9.6
+    (5, 104, 4, 256, 18, 30, TOK32),       # 5.1 / 7.6
+    (2, 111, 1, 128, 65, 33, TOK32),       # 4.3 / 12.6
+    (32, 7, 32, 192, 192, 320, TOK32),     # 33.8 / 38.5
+    (32, 70, 2, 64, 1, 33, TOK32),         # 4.5 / 10.8
+    # many: the GEMM
+    (1, 300, 16, 512, 96, 160, GEMM1),     # 24.4 / 20.1
+    (1, 3000, 16, 512, 36, 60, GEMM2),     # 75.7 / 26.4
+    (1, 200, 16, 512, 288, 480, GEMM1),    # 41.5 / 29.5
+    (2, 3001, 16, 512, 192, 320, GEMM2),
+    (4, 8192, 16, 512, 288, 480, GEMM2),
+    (1, 300, 1, 8192, 288, 480, GEMM1),    # an LLA-2D prompt
+    (1, 2500, 16, 320, 288, 480, GEMM1),   # 6 rounds of 32 tokens per wavefront, 4 of 64
+    # other kernels
+    (1, 64, 16, 512, 96, 160, FEW),
+    (2, 4096, 16, 512, 18, 30, STREAM),
+    (1, 3000, 16, 96, 192, 320, TOK32),    # K not a multiple of 64
+])
+def test_encode_route(host, B, M, H, K, r_k, r_v, route):
+    assert encode_route(host, B, M, H, K, r_k, r_v)[0] == route

@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2607_15456_amd import lla, workloads as W
-from tests.helpers import assert_close, assert_units_close, f64, f64_dev, log, round_bf16
+from tests.helpers import GEMM1, GEMM2, TOK32, assert_close, assert_units_close, encode_route, f64, f64_dev, log, round_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -42,6 +42,20 @@ def _check(wl, inputs, ck, cv, pos0, M, dtype, what):
         assert_close(got[:, :, pos0:pos0 + M], ref, dtype, f"{what} {name}")
         untouched = np.concatenate([got[:, :, :pos0].ravel(), got[:, :, pos0 + M:].ravel()])
         assert np.all(untouched == SENTINEL), f"{what} {name}: slots outside [pos0, pos0+M) changed"
+
+
+def _check_rounded(inputs, ck, cv, pos0, M):
+    """The stored value is the fp32 sum rounded to bf16: half an ulp is at most
+    2^-8 of the value; the sums themselves (terms of variance 1/K, with the mean's
+    subtracted) are good to 1e-3 by far.  For caches of so many values that some
+    exceed 8, whose rounding alone is above a max-abs of 2e-2."""
+    xk, xv, wk, wv, muk, muv = inputs
+    for x, w, mu, c in ((xk, wk, muk, ck), (xv, wv, muv, cv)):
+        ref = oracle.encode_batched(f64(x), None if mu is None else f64(mu), f64(w))
+        got = f64(lla.from_paged(c))
+        new = got[:, :, pos0:pos0 + M]
+        assert np.all(np.abs(new - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-3)
+        assert np.all(got[:, :, :pos0] == SENTINEL) and np.all(got[:, :, pos0 + M:] == SENTINEL)
 
 
 def test_tiny_fp32_encode():
@@ -136,6 +150,22 @@ def test_encode_many_tokens(r_k, r_v, T, d, B, M, pos0):
     _check(wl, inputs, ck, cv, pos0, M, torch.bfloat16, f"M={M}")
 
 
+@pytest.mark.parametrize("r_k,r_v,T,d,H,B,M,pos0", [
+    (33, 17, 1, 96, 3, 1, 8200, 60),   # K an odd multiple of 32
+    (150, 40, 3, 32, 2, 3, 2800, 5),   # more than 8 row tiles: two chunks of them
+    (8, 30, 1, 64, 1, 2, 4100, 1),     # too little work for the GEMM
+])
+def test_encode_many_tokens_32(r_k, r_v, T, d, H, B, M, pos0):
+    """Writes of 8192 tokens and more on the 32-token kernel: a workgroup takes
+    all heads of its tokens."""
+    wl = W.Workload(f"enc_many32_{T}_{d}", 1, H, d, T, B, 0, ((r_k, r_v),), torch.bfloat16)
+    n_max = ((pos0 + M + 63) // 64) * 64 + 64
+    assert encode_route(lla.lib(), B, M, H, T * d, r_k, r_v, pos0)[0] == TOK32
+    log(f"encode many tokens r=({r_k},{r_v}) K={T * d} H={H} B={B} M={M} pos0={pos0}")
+    inputs, ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, True, torch.bfloat16)
+    _check(wl, inputs, ck, cv, pos0, M, torch.bfloat16, f"M={M}")
+
+
 @pytest.mark.parametrize("r_k,r_v,T,d,B,M,pos0", [
     (96, 160, 4, 128, 2, 300, 5),      # the 4x tier, K = 512, ragged token block
     (288, 480, 4, 128, 1, 1000, 64),   # the 1.33x tier
@@ -146,7 +176,8 @@ def test_encode_many_tokens(r_k, r_v, T, d, B, M, pos0):
 @pytest.mark.parametrize("means", [False, True])
 def test_encode_many_tokens_tier_ranks(r_k, r_v, T, d, B, M, pos0, means):
     """Prompt-sized writes at the paper's per-head rank tiers: the MFMA GEMM path."""
-    wl = W.Workload(f"enc_tier_{T}_{d}", 1, 4, d, T, B, 0, ((r_k, r_v),), torch.bfloat16)
+    wl = W.Workload(f"enc_tier_{T}_{d}", 1, 8, d, T, B, 0, ((r_k, r_v),), torch.bfloat16)
+    assert encode_route(lla.lib(), B, M, wl.H, T * d, r_k, r_v, pos0)[0] in (GEMM1, GEMM2)
     n_max = ((pos0 + M + 63) // 64) * 64 + 64
     log(f"encode tier ranks r=({r_k},{r_v}) K={T * d} B={B} M={M} pos0={pos0} means={means}")
     inputs, ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, means, torch.bfloat16)
@@ -154,27 +185,24 @@ def test_encode_many_tokens_tier_ranks(r_k, r_v, T, d, B, M, pos0, means):
 
 
 @pytest.mark.parametrize("r_k,r_v,T,d,H,B,M,pos0,runs", [
-    # 3 row blocks x 48 token blocks x 15 heads: 2 heads per workgroup, the last group 1
-    (96, 160, 4, 128, 15, 2, 6000, 5, 2),
-    # 8 row blocks x 24 token blocks x 16 heads: 3 heads per workgroup, the last group 1
-    (288, 480, 4, 128, 16, 1, 4100, 64, 3),
-    # K = 192: an odd chunk count per head, so one head per workgroup
-    (96, 160, 3, 64, 16, 1, 12000, 0, 1),
+    (96, 160, 1, 64, 15, 2, 11900, 5, 2),      # one chunk per head; the last run 1
+    (288, 480, 2, 64, 16, 1, 12230, 3, 3),     # two chunks; the last run 1
+    (288, 480, 2, 128, 15, 1, 10190, 3, 2),    # four; the last run 1
+    (96, 160, 3, 64, 16, 1, 22100, 0, 2),      # three
+    (288, 480, 4, 128, 16, 1, 1000, 64, 1),    # 32 tokens per wavefront: always one head
 ])
 @pytest.mark.parametrize("means", [False, True])
 def test_encode_gemm_head_runs(r_k, r_v, T, d, H, B, M, pos0, runs, means):
-    """Prompt-sized per-head writes where a GEMM workgroup walks a run of heads
-    (as many as keep 1024 workgroups), including a last run shorter than the
+    """Prompt-sized per-head writes where a GEMM workgroup walks a run of heads,
+    over odd and even chunk counts and including a last run shorter than the
     others; every latent is checked against the oracle."""
-    ntb = (B * M + 255) // 256
-    blocks = ((r_k + 95) // 96 + (r_v + 95) // 96) * ((ntb + 7) // 8 * 8)
-    nkc = T * d // 64
-    assert runs == (1 if nkc % 2 else max(1, min(H, H * blocks // 1024))), "case no longer takes the intended runs"
+    route, heads, _, _ = encode_route(lla.lib(), B, M, H, T * d, r_k, r_v, pos0)
+    assert (route, heads) == (GEMM2 if runs > 1 else GEMM1, runs), "case no longer takes the intended runs"
     wl = W.Workload(f"enc_runs_{T}_{d}_{H}", 1, H, d, T, B, 0, ((r_k, r_v),), torch.bfloat16)
     n_max = ((pos0 + M + 63) // 64) * 64 + 64
     log(f"encode head runs r=({r_k},{r_v}) K={T * d} H={H} B={B} M={M} pos0={pos0} runs={runs} means={means}")
     inputs, ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, means, torch.bfloat16)
-    _check(wl, inputs, ck, cv, pos0, M, torch.bfloat16, f"H={H} M={M}")
+    _check_rounded(inputs, ck, cv, pos0, M)
 
 
 @pytest.mark.parametrize("r_k,r_v,means", [(96, 160, False), (200, 8, True)])
@@ -183,7 +211,8 @@ def test_encode_gemm_ring_slots(r_k, r_v, means):
     sink + window ring cache whose positions wrap: every kept position's slot
     holds the oracle's latent of that token (later tokens overwrite earlier ones)."""
     sink, window, chunks = 4, 512, [300, 500, 260]  # at most `window` tokens per call
-    wl = W.Workload("enc_ring_gemm", 1, 4, 128, 4, 2, 0, ((r_k, r_v),), torch.bfloat16)
+    wl = W.Workload("enc_ring_gemm", 1, 8, 128, 4, 2, 0, ((r_k, r_v),), torch.bfloat16)
+    assert all(encode_route(lla.lib(), 2, m, 8, 512, r_k, r_v)[0] in (GEMM1, GEMM2) for m in chunks)
     B, H, K = wl.B, wl.H, wl.T * wl.d
     n_max = ((sink + window + 63) // 64) * 64
     wk = W.down_projection(wl, r_k, "k", 0, DEV, torch.bfloat16)
@@ -224,37 +253,36 @@ def test_fp32_tiles(r_k, r_v, M, pos0, d_head):
 
 @pytest.mark.parametrize("r_k,r_v", [(33, 65), (160, 97), (96, 320), (36, 60)])
 @pytest.mark.parametrize("B,M,pos0,T,d_head", [(1, 192, 0, 4, 128), (3, 171, 5, 4, 128), (2, 601, 61, 2, 96),
-                                               (40, 13, 7, 1, 64), (90, 3, 5, 1, 64), (2, 1500, 3, 4, 128)])
+                                               (40, 13, 7, 1, 64), (90, 3, 5, 1, 64), (2, 1997, 3, 4, 128)])
 @pytest.mark.parametrize("means", [False, True])
 def test_gemm_tiles(r_k, r_v, B, M, pos0, T, d_head, means):
     """The GEMM write at the edges of its blocks: row blocks of 3, 2 and 1
     tiles, token blocks cut per sequence (odd lengths and positions) and over
     short sequences, an odd number of K-chunks (K = 192), one chunk (K = 64),
     32 and 64 tokens per wavefront."""
-    wl = W.Workload("enc_gemm", 1, 16 if M == 1500 else 3, d_head, T, B, 0, ((18, 30),), torch.bfloat16)
+    if max(r_k, r_v) <= 64 and B * M < 256:
+        M = 257  # the fewest tokens that take the GEMM at these ranks
+    want = GEMM2 if M == 1997 else GEMM1
+    H = next(h for h in (3, 5, 9, 17, 33, 48, 65, 97, 129, 193)
+             if encode_route(lla.lib(), B, M, h, T * d_head, r_k, r_v, pos0)[0] == want)
+    wl = W.Workload("enc_gemm", 1, H, d_head, T, B, 0, ((18, 30),), torch.bfloat16)
     n_max = (pos0 + M + 63) // 64 * 64 + 64
-    log(f"encode gemm r=({r_k},{r_v}) B={B} M={M} pos0={pos0} K={T * d_head} means={means}")
-    (xk, xv, wk, wv, muk, muv), ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, means, torch.bfloat16)
-    for x, w, mu, c in ((xk, wk, muk, ck), (xv, wv, muv, cv)):
-        ref = oracle.encode_batched(f64(x), None if mu is None else f64(mu), f64(w))
-        got = f64(lla.from_paged(c))
-        new = got[:, :, pos0:pos0 + M]
-        # the stored value is the fp32 sum rounded to bf16: half an ulp is at most
-        # 2^-8 of the value; the sums themselves (512 terms of variance 1/512, with
-        # the mean's subtracted) are good to 1e-3 by far
-        assert np.all(np.abs(new - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-3)
-        assert np.all(got[:, :, :pos0] == SENTINEL) and np.all(got[:, :, pos0 + M:] == SENTINEL)
+    log(f"encode gemm r=({r_k},{r_v}) B={B} M={M} pos0={pos0} H={H} K={T * d_head} means={means}")
+    inputs, ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, means, torch.bfloat16)
+    _check_rounded(inputs, ck, cv, pos0, M)
 
 
 @pytest.mark.parametrize("pos0", [0, 203, 1001])
 def test_gemm_ring(pos0):
     """The GEMM write into a sink + window budget: pieces that are 8 consecutive
     aligned slots, and those that cross the ring's end or the sink."""
-    wl = W.Workload("enc_ring", 1, 3, 128, 4, 2, 0, ((18, 30),), torch.bfloat16)
+    H = 6
+    wl = W.Workload("enc_ring", 1, H, 128, 4, 2, 0, ((18, 30),), torch.bfloat16)
     B, M, r_k, r_v, sink, window = 2, 350, 96, 160, 4, 380
+    assert encode_route(lla.lib(), B, M, H, 512, r_k, r_v)[0] in (GEMM1, GEMM2)
     xk, xv, wk, wv, muk, muv = _inputs(wl, r_k, r_v, B, M, True, torch.bfloat16)
-    ck = torch.full((B, 3, 6, r_k, 64), SENTINEL, dtype=torch.bfloat16, device=DEV)
-    cv = torch.full((B, 3, 6, r_v, 64), SENTINEL, dtype=torch.bfloat16, device=DEV)
+    ck = torch.full((B, H, 6, r_k, 64), SENTINEL, dtype=torch.bfloat16, device=DEV)
+    cv = torch.full((B, H, 6, r_v, 64), SENTINEL, dtype=torch.bfloat16, device=DEV)
     lla.encode(xk, xv, wk, wv, ck, cv, T=4, pos0=pos0, mu_k=muk, mu_v=muv, evict=(sink, window))
     p = np.arange(pos0, pos0 + M)
     slot = np.where(p < sink, p, sink + (p - sink) % window)
