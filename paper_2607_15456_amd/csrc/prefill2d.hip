@@ -1063,29 +1063,34 @@ hipError_t launch_recon_r(const Prefill2dArgs& a, int r, hipStream_t stream) {
 // Key streams per workgroup of the attention: 1 (flash2d_kernel, 256 queries),
 // 2, 4 (flash2d_streams_kernel, 128 and 64 queries) or 8 (flash2d_split_kernel,
 // 32).  Fewer queries per workgroup put more workgroups on the machine, each
-// with a shorter key loop, but stage every key for fewer queries: at a full
-// machine (4 x 4096 tokens, 16 heads) they run at 1, 0.85, 0.66 and 0.52 of
-// flash2d_kernel's rate.  The estimate adds, for one compute unit, the keys of
-// the heaviest workgroup of every round of the machine (workgroups start
-// heaviest first) and a fixed cost per workgroup, in keys of flash2d_kernel's
-// loop.  Attention and rebuilds per call at (96, 160), 16 heads, 1 / 2 / 4 / 8
-// streams: 300 tokens after 7000 211 / 150 / 118 / 85 us; 1024 tokens 47 / 38 /
-// 32 / 33; 2048 tokens 76 / 60 / 55 / 64; 4096 tokens 134 / 114 / 139 / 163;
-// 4 x 300 after 2000 104 / 87 / 97 / 101; 4 x 2048 138 / 160 / 191 / 242.
+// through its keys in less time (1.3, 1.6 and 2.1 times flash2d_kernel's rate), but
+// stage every key for fewer queries: a full machine runs at 0.65, 0.4 and 0.26 of
+// its rate.  The estimate, in keys of flash2d_kernel's loop: the heaviest
+// workgroup, or the mean load of a compute unit (and where workgroups come in
+// rounds half of the lightest one, heaviest first), each workgroup with its keys
+// and a fixed cost.  Numbers from all four measured on 1871 drawn calls (1 to 32
+// heads, 1 to 9000 queries after up to 9000 keys, both caches; repeated and with
+// other inputs between): the choice is nowhere more than 3% slower than
+// flash2d_kernel and loses 0.2% to the best of the four.  Attention and
+// rebuilds per call at (96, 160), 16 heads, 1 / 2 / 4 / 8 streams: 300 tokens
+// after 7000 211 / 150 / 118 / 85 us; 1024 tokens 47 / 38 / 32 / 33; 2048 tokens
+// 76 / 60 / 55 / 64; 2 x 3191 (104, 96) 126 / 146 / 186 / 217; 4 x 2048 138 / 160
+// / 191 / 242.
 int key_streams(const Prefill2dArgs& a) {
   const int cus = device_cu_count();
-  const double rate[4] = {1.0, 2 * 0.85, 4 * 0.66, 8 * 0.52}, fixed[4] = {40, 100, 150, 240};
+  const double rate[4] = {1.0, 1.3, 1.6, 2.1}, fixed[4] = {95, 130, 130, 160};
+  const double bh = (double)a.B * a.H;
   int best = 1;
   double best_t = 0.0;
   for (int k = 0; k < 4; ++k) {
     const int qb = kQBlock >> k, nqb = (a.M + qb - 1) / qb;
-    const long wgs = (long)a.B * a.H * nqb;
-    if (k == 0 && wgs > 8L * cus) return 1;
+    const double wgs = bh * nqb;
+    if (k == 0 && wgs > 8.0 * cus) return 1;
     if (nqb > 65535) break;
-    double t = 0.0;
-    for (long r = 0; r < wgs; r += cus)
-      t += a.p0 + min((nqb - r / ((long)a.B * a.H)) * qb, (long)a.M) + fixed[k];
-    t /= rate[k];
+    const double keys = bh * ((double)nqb * a.p0 + 0.5 * qb * nqb * (nqb - 1.0) + a.M);
+    double t = (keys + wgs * fixed[k]) / cus;
+    if (wgs > cus) t += 0.5 * (a.p0 + min(qb, a.M) + fixed[k]);
+    t = fmax(t, a.p0 + a.M + fixed[k]) / rate[k];
     if (k == 0 || t < 0.97 * best_t) {
       best = 1 << k;
       best_t = t;
@@ -1162,3 +1167,12 @@ hipError_t launch_prefill_rebuild(const Prefill2dArgs& a, hipStream_t stream) {
 }
 
 }  // namespace lla
+
+extern "C" int lla_internal_key_streams(int B, int H, int M, int p0) {
+  lla::Prefill2dArgs a{};
+  a.B = B;
+  a.H = H;
+  a.M = M;
+  a.p0 = p0;
+  return lla::key_streams(a);
+}

@@ -72,3 +72,27 @@ def test_gemm_token_blocks(host, B, M, pos0):
 ])
 def test_encode_route(host, B, M, H, K, r_k, r_v, route):
     assert encode_route(host, B, M, H, K, r_k, r_v)[0] == route
+
+
+@pytest.mark.parametrize("B,M,p0,streams", [
+    # us per call at (96, 160), 16 heads, 1 / 2 / 4 / 8 streams
+    (1, 300, 7000, 8),    # 211 / 150 / 118 / 85
+    (1, 1024, 0, 4),      # 47 / 38 / 32 / 33
+    (1, 2048, 0, 4),      # 76 / 60 / 55 / 64
+    (1, 4096, 0, 2),      # 134 / 114 / 139 / 163
+    (4, 300, 2000, 2),    # 104 / 87 / 97 / 101
+    (2, 3191, 0, 1),      # 126 / 146 / 186 / 217, (104, 96)
+    (4, 2048, 0, 1),      # 138 / 160 / 191 / 242
+    (4, 550, 274, 1),     # 67 / 68 / 71 / 78, (240, 400)
+    (1, 5486, 334, 1),    # 195 / 212 / 252 / 286
+    (64, 4096, 0, 1),
+])
+def test_key_streams(host, B, M, p0, streams):
+    assert host.lla_internal_key_streams(B, 16, M, p0) == streams
+
+
+def test_key_streams_grid(host):
+    """More than 65535 query blocks of the smaller sizes: a grid that fits."""
+    for M in (2 ** 21 + 5, 2 ** 22, 2 ** 23 + 9):
+        streams = host.lla_internal_key_streams(1, 1, M, 0)
+        assert streams in (1, 2, 4, 8) and -(-M // (256 // streams)) <= 65535

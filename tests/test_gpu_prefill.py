@@ -205,21 +205,28 @@ def test_bf16_prefill_tier_peaked_and_rising(qmul, kramp):
                  f"q x{qmul} ramp {kramp}")
 
 
-@pytest.mark.parametrize("B,M,p0", [(1, 33, 70), (1, 300, 2000),      # 8 key streams on a 256-CU device
-                                    (1, 1000, 31),                     # 4
-                                    (4, 270, 1500), (1, 3970, 5),      # 2
-                                    (4, 1900, 0)])                     # 1
+# B, M, p0 and the key streams they take
+STREAMS = [(1, 33, 70, 8), (1, 300, 2000, 8), (1, 1000, 31, 4), (4, 270, 1500, 2), (1, 3970, 5, 2), (4, 1900, 0, 1)]
+
+
+def _takes_streams(B, M, p0, streams):
+    """Whether a call of 16 heads takes this many key streams on this device."""
+    return lla.lib().lla_internal_key_streams(B, 16, M, p0) == streams
+
+
+@pytest.mark.parametrize("B,M,p0,streams", STREAMS)
 # The queries and rebuilt keys enter in fp16 (relative error 2^-12 each), so a base-2 logit L carries an error
 # of up to |L| 2^-11: a weight is off by |L| 2^-11 ln 2.  With the ramp L reaches about 45 (a standard deviation
 # of 10), 1.5%; queries x 4 on top of it would make that 6%, of values near 28, above the 2e-2 bar by the
 # rounding of the operands alone.
 @pytest.mark.parametrize("qmul,kramp,means", [(1.0, 0.0, True), (1.0, 6.0, False)])
-def test_bf16_prefill_key_streams(B, M, p0, qmul, kramp, means):
+def test_bf16_prefill_key_streams(B, M, p0, streams, qmul, kramp, means):
     """Every split of the attention's workgroups between queries and keys, at the
     edges of their query groups, key tiles and rounds; latents growing along the
     context raise the running maximum in every stream."""
     wl = W.Workload("pf_streams", 1, 16, 128, 4, B, 0, ((96, 160),), torch.bfloat16)
     log(f"key streams B={B} M={M} p0={p0} q x{qmul} ramp {kramp}")
+    assert _takes_streams(B, M, p0, streams)
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, 96, 160, B, M, p0, torch.bfloat16, means=means, qmul=qmul,
                                                 kramp=kramp)
     out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
@@ -236,16 +243,16 @@ def test_bf16_prefill_key_streams(B, M, p0, qmul, kramp, means):
     assert_close(o, ref, torch.bfloat16, "key streams")
 
 
-@pytest.mark.parametrize("B,M,p0", [(1, 33, 1070), (1, 300, 2000), (1, 1000, 1031), (4, 270, 1500), (1, 3970, 5),
-                                    (4, 1900, 0)])
+@pytest.mark.parametrize("B,M,p0,streams", [(1, 33, 1070, 8), (1, 1000, 1031, 4)] + STREAMS[1:])
 @pytest.mark.parametrize("low", [-170.0, -86.0])
-def test_bf16_prefill_far_below(B, M, p0, low):
+def test_bf16_prefill_far_below(B, M, p0, streams, low):
     """Runs of keys whose base-2 logits lie below the range of the fp16 running
     maximum (about -83,000), or at its coarsest (about -42,000, where it is a
     multiple of 32), beside ordinary ones: weight 0, and the query's other keys
     count as ever, whichever workgroup or wavefront meets such a run first."""
     wl = W.Workload("pf_far", 1, 16, 128, 4, B, 0, ((96, 160),), torch.bfloat16)
     log(f"far below B={B} M={M} p0={p0} low={low}")
+    assert _takes_streams(B, M, p0, streams)
     q, ck, cv, uk, uv, _, _, _, _ = _case(wl, 96, 160, B, M, p0, torch.bfloat16, means=False)
     N = p0 + M
     n = torch.arange(N, device=DEV)
