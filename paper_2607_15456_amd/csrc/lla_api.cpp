@@ -91,20 +91,36 @@ int row_blocks_of(int r_k, int r_v, int d_rope) {
   return std::max((r_k + 7) / 8 + d_rope / 8, (r_v + 7) / 8);
 }
 
-// fp32 decode: the matrix kernel (one 8-wavefront workgroup per slice, each
-// wavefront on a page) or the scan.  Four calls over 16 heads, matrix against
-// scan: one sequence of 512 tokens (96, 160) 97 / 104 us, of 1500 at two
-// sequences 123 / 279, (192, 320) 2048 tokens 196 / 776; from 129 units the
-// scan's wavefronts already stream side by side ((96, 160) 16 x 1024 266 / 208)
-// except at r_v > 256, where its rows no longer fit the registers ((192, 320)
-// 64 x 2048 2986 / 3632).  At r_v <= 32 most of the matrix kernel's wavefronts
-// have no value tile (4 x 4096 118 / 90).  Contexts of 64 pages and more over
-// few units keep the scan and its split counts, which lla_decode_splits
-// reports.
-bool f32_matrix_decode(int units, int pages, int r_v) {
-  const int cus = lla::device_cu_count();
-  if (r_v > 256) return pages < 64 || units >= cus;
-  return r_v > 32 && pages < 64 && 2 * units <= cus;
+// fp32 decode: slices of a context in the matrix kernel, of at least 8 pages, one
+// workgroup per compute unit at most (1500 tokens of two sequences, 16 heads, (96,
+// 160), four calls: 3 slices 123 us, 12 of 2 pages 158).
+int f32_slices(int units, int pages, bool allow_split) {
+  return allow_split ? std::max(1, std::min(lla::device_cu_count() / units, pages / 8)) : 1;
+}
+
+// fp32 decode: the matrix kernel (one 8-wavefront workgroup per slice, a page per
+// wavefront, the 16-row value tiles dealt over the wavefronts) or the scan.  Drawn
+// from 1350 calls (1 to 2048 units, 1 to 9000 tokens, ranks 1 to 512, d_head 32 to
+// 256, repeated and with other inputs between); the choice is nowhere more than 3%
+// slower than the scan.  One call, scan / matrix, repeated inputs:
+//  - r_v > 256, where the scan's rows no longer fit its registers: the matrix
+//    kernel ((288, 480) 1 token 101 / 33 us, 2500 tokens of 128 units 581 / 222),
+//    but one workgroup does not walk more than 32 pages alone while compute units
+//    are idle ((192, 320) 3912 tokens of 32 units, no workspace 267 / 306), nor
+//    one page for more than two of them per unit ((192, 320) 114 / 132).
+//  - 64 < r_v <= 256 over few units: where slices keep it at 16 pages at most ((96,
+//    160) 1573 tokens 54 / 32, (48, 80) and up), and above 128 also a single group
+//    of 8 pages (512 tokens 26 / 24; 858 tokens in one slice 33 / 40).  A r_v that is
+//    not a multiple of 4 reads U_v by the element ((80, 130) 1 token 18 / 19).
+//  - r_v <= 64: half of the wavefronts and more have no value tile ((64, 64) 1
+//    token 10.9 / 12.0, (36, 60) 3756 tokens without a workspace 21 / 61).
+// Contexts of 64 pages and more over few units keep the scan's split counts, which
+// lla_decode_splits reports.
+bool f32_matrix_decode(int units, int pages, int slices, int r_v) {
+  const int cus = lla::device_cu_count(), per = (pages + slices - 1) / slices;
+  if (r_v > 256) return units >= cus ? pages >= 2 || units <= 2 * cus : pages < 64 && per <= 32;
+  if (r_v <= 64 || r_v % 4 || pages >= 64 || 2 * units > cus) return false;
+  return slices > 1 ? per <= 16 : r_v > 128 && per <= 8;
 }
 
 // fp32 prefill: a 16-query tile of the matrix kernel costs about what the
@@ -130,12 +146,10 @@ DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int 
   static const int forced_short_groups = env_int("LLA_DECODE_SHORT_GROUPS");
   const int pages = (n_ctx + LLA_PAGE_TOKENS - 1) / LLA_PAGE_TOKENS;
   const int groups = (pages + 7) / 8;
-  if (!bf16 && !forced_waves && f32_matrix_decode(units, pages, r_v)) {
-    // slices of at least 8 pages, one workgroup per compute unit at most (1500
-    // tokens of two sequences: 3 slices 123 us, 12 of 2 pages 158)
-    long s = allow_split ? std::min<long>(lla::device_cu_count() / units, pages / 8) : 1L;
-    if (forced_splits > 0 && allow_split) s = std::min(forced_splits, max_splits(n_ctx));
-    return DecodeShape{8, (int)std::max(1L, s), 0, 0, 0, 1};
+  const int slices = f32_slices(units, pages, allow_split);
+  if (!bf16 && !forced_waves && f32_matrix_decode(units, pages, slices, r_v)) {
+    const bool forced = forced_splits > 0 && allow_split;
+    return DecodeShape{8, forced ? std::min(forced_splits, max_splits(n_ctx)) : slices, 0, 0, 0, 1};
   }
   const long target = 8L * lla::device_cu_count();  // resident wavefronts wanted
   // bf16: the software-pipelined variant (two batches of loads in flight per
@@ -262,6 +276,11 @@ double lla_internal_rope_frequency(double base, double c) {
   double hi, lo;
   lla::log2_parts(base, &hi, &lo);
   return lla::rope_frequency(hi, lo, c);
+}
+
+// Whether an fp32 decode takes the matrix kernel.
+int lla_internal_f32_matrix_decode(int B, int H, int n_ctx, int r_v, int with_workspace) {
+  return choose_shape(B * H, n_ctx, with_workspace != 0, false, 1, r_v).matrix;
 }
 
 const char* lla_status_string(int status) {

@@ -96,3 +96,26 @@ def test_key_streams_grid(host):
     for M in (2 ** 21 + 5, 2 ** 22, 2 ** 23 + 9):
         streams = host.lla_internal_key_streams(1, 1, M, 0)
         assert streams in (1, 2, 4, 8) and -(-M // (256 // streams)) <= 65535
+
+
+@pytest.mark.parametrize("B,H,n_ctx,r_v,workspace,matrix", [
+    # us, scan / matrix
+    (1, 16, 512, 160, 1, 1),      # 26 / 24
+    (1, 16, 858, 160, 1, 0),      # 33 / 40
+    (1, 4, 1573, 160, 1, 1),      # 54 / 32
+    (1, 16, 2833, 160, 0, 0),     # 106 / 133
+    (1, 16, 8000, 160, 1, 0),
+    (16, 16, 512, 160, 1, 0),
+    (1, 16, 1, 64, 1, 0),         # 10.9 / 12.0
+    (1, 16, 3756, 60, 0, 0),      # 21 / 61
+    (1, 16, 1500, 128, 1, 1),
+    (1, 16, 1500, 128, 0, 0),
+    (1, 8, 4, 130, 1, 0),         # 18 / 20
+    (1, 16, 1, 480, 1, 1),        # 101 / 33
+    (8, 16, 2551, 480, 1, 1),     # 581 / 222
+    (1, 32, 3912, 320, 0, 0),     # 267 / 306
+    (32, 32, 6, 320, 1, 0),       # 114 / 132
+    (64, 16, 2048, 320, 1, 1),
+])
+def test_f32_decode(host, B, H, n_ctx, r_v, workspace, matrix):
+    assert host.lla_internal_f32_matrix_decode(B, H, n_ctx, r_v, workspace) == matrix

@@ -58,15 +58,18 @@ def test_nonfinite_reaches_only_its_queries(axis, value, n_bad):
         assert kinds.all() and np.isnan(hit).any()
 
 
-@pytest.mark.parametrize("r_k,r_v", [(36, 60), (96, 160), (192, 320)])
-@pytest.mark.parametrize("N,lens", [(64, [64, 1]), (513, [513, 65]), (1500, [1500, 700]), (4000, [3968, 64])])
+# with a workspace (split) or short the matrix kernel, with one, two or four value tiles per wavefront; else the scan
+@pytest.mark.parametrize("r_k,r_v", [(48, 80), (96, 160), (192, 320), (300, 257)])
+@pytest.mark.parametrize("N,lens", [(64, [64, 1]), (513, [513, 65]), (1500, [1500, 700]), (2048, [2048, 1985]),
+                                    (4000, [3968, 64])])
 @pytest.mark.parametrize("split", [False, True])
 def test_decode_short_contexts(r_k, r_v, N, lens, split):
     wl = W.Workload("f32_decode", 1, 8, 128, 4, 2, N, ((r_k, r_v),), F32)
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 2, N, 0, F32)
     q = q[:, :, 0].contiguous()
     ws = lla.new_workspace(2, 8, r_v, N) if split else None
-    log(f"decode fp32 r=({r_k},{r_v}) N={N} splits={lla.decode_splits(F32, 2, 8, N, r_k, r_v, with_workspace=split)}")
+    log(f"decode fp32 r=({r_k},{r_v}) N={N} splits={lla.decode_splits(F32, 2, 8, N, r_k, r_v, with_workspace=split)} "
+        f"matrix={lla.lib().lla_internal_f32_matrix_decode(2, 8, N, r_v, int(split))}")
     for cur in (lens, lens[::-1]):
         out = lla.decode_attn(q, pk, pv, uk, uv, n_ctx=N, ctx_len=torch.tensor(cur, dtype=torch.int32, device=DEV),
                               mu_k=muk, mu_v=muv, workspace=ws)
