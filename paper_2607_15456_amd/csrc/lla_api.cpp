@@ -123,17 +123,23 @@ bool f32_matrix_decode(int units, int pages, int slices, int r_v) {
   return slices > 1 ? per <= 16 : r_v > 128 && per <= 8;
 }
 
-// fp32 prefill: a 16-query tile of the matrix kernel costs about what the
-// scan's workgroups for 16 queries at r_v = 30 do, less at larger ranks or
-// more queries (four calls, one sequence of 16 heads, matrix / scan: 16
-// queries after 2000 tokens (18, 30) 117 / 96 us, (36, 60) 151 / 157, (96, 160)
-// 310 / 339; 64 queries 128 / 200, 170 / 369, 334 / 1031; a 500-token prompt
-// (96, 160) 165 / 1190).  Fewer queries only where the call is short and the
-// machine is not full (1 query after 100 tokens (96, 160) 77 / 115), or at
-// r_v > 256 (after 8000 tokens 3010 / 5648).
-bool f32_matrix_prefill(int units, int M, int keys, int r_v) {
-  if (M >= 32 || r_v > 256 || (M >= 16 && r_v > 32)) return true;
-  return keys <= 512 && 2 * units <= lla::device_cu_count();
+// fp32 prefill: the matrix kernel takes 16 queries of a unit per workgroup, the scan
+// one.  Few queries in all run side by side in the scan, whose workgroups are the
+// shorter ones, so below 1024 queries over all units (four workgroups per compute
+// unit) the matrix kernel is kept for ranks where a tile costs less than the
+// scan's slowest query; drawn from 1350 calls (1 to 1024 units, 1 to 700 queries
+// after up to 4000 keys, ranks 1 to 512, d_head 32 to 256, repeated and with other
+// inputs between), one of which is slower than the scan by 8%.  One call, scan /
+// matrix: 500 queries of 16 heads (96, 160) 305 / 38 us, 431 of 256 units (16, 16)
+// 844 / 200; 350 queries of one head after 3729 keys (65, 33) 55 / 86, 59 of 4
+// units after 3270 (8, 8) 14 / 42; 16 queries of 16 heads (96, 160) after 2000
+// keys 85 / 78, at (18, 30) 24 / 29 (32 from there on); r_v > 256, one query after
+// 8000 keys 1412 / 753.
+bool f32_matrix_prefill(int units, int M, int r_v) {
+  if (r_v > 256) return true;
+  if (M < 16) return false;
+  if (r_v > 128 && r_v % 4 == 0) return true;
+  return (int64_t)units * M >= 4 * lla::device_cu_count() && (M >= 32 || r_v > 32);
 }
 
 DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int row_blocks, int r_v) {
@@ -282,6 +288,9 @@ double lla_internal_rope_frequency(double base, double c) {
 int lla_internal_f32_matrix_decode(int B, int H, int n_ctx, int r_v, int with_workspace) {
   return choose_shape(B * H, n_ctx, with_workspace != 0, false, 1, r_v).matrix;
 }
+
+// Whether an fp32 prefill takes the matrix kernel.
+int lla_internal_f32_matrix_prefill(int B, int H, int M, int r_v) { return f32_matrix_prefill(B * H, M, r_v); }
 
 const char* lla_status_string(int status) {
   switch (status) {
@@ -768,7 +777,7 @@ lla_status prefill_impl(int dtype, int out_dtype, int B, int H, int M, int d_hea
   a.splits = 1;
   a.waves = 4;
   a.deep = 0;
-  a.matrix = f32_matrix_prefill(B * H, M, p0 + M, r_v) ? 1 : 0;
+  a.matrix = f32_matrix_prefill(B * H, M, r_v) ? 1 : 0;
   a.q = q;
   a.ck = c_k;
   a.cv = c_v;

@@ -196,4 +196,5 @@ int lla_internal_encode_route(int B, int M, int H, int K, int r_k, int r_v, int 
                               int* rounds);
 int lla_internal_key_streams(int B, int H, int M, int p0);
 int lla_internal_f32_matrix_decode(int B, int H, int n_ctx, int r_v, int with_workspace);
+int lla_internal_f32_matrix_prefill(int B, int H, int M, int r_v);
 }

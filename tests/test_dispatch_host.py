@@ -119,3 +119,21 @@ def test_key_streams_grid(host):
 ])
 def test_f32_decode(host, B, H, n_ctx, r_v, workspace, matrix):
     assert host.lla_internal_f32_matrix_decode(B, H, n_ctx, r_v, workspace) == matrix
+
+
+@pytest.mark.parametrize("B,H,M,r_v,matrix", [
+    # us, scan / matrix
+    (1, 16, 500, 160, 1),    # 305 / 38
+    (32, 8, 431, 16, 1),     # 844 / 200
+    (1, 1, 350, 33, 0),      # 55 / 86, after 3729 keys
+    (2, 2, 59, 8, 0),        # 14 / 42, after 3270 keys
+    (1, 16, 64, 30, 1),      # 50 / 32, after 2000 keys
+    (1, 16, 63, 30, 0),
+    (64, 16, 31, 30, 0),
+    (1, 16, 16, 160, 1),     # 85 / 78, after 2000 keys
+    (4, 2, 13, 160, 0),      # 22 / 24
+    (1, 1, 38, 162, 0),      # not a multiple of 4
+    (1, 1, 1, 320, 1),
+])
+def test_f32_prefill(host, B, H, M, r_v, matrix):
+    assert host.lla_internal_f32_matrix_prefill(B, H, M, r_v) == matrix

@@ -17,32 +17,52 @@ pytestmark = pytest.mark.gpu
 DEV, F32 = "cuda", torch.float32
 
 
+def _heads(M, r_v):
+    """The fewest of some head counts with which one sequence's M queries take the matrix kernel."""
+    return next(h for h in (3, 16, 35, 66) if lla.lib().lla_internal_f32_matrix_prefill(1, h, M, r_v))
+
+
 @pytest.mark.parametrize("r_k,r_v", [(18, 30), (33, 17), (1, 1), (96, 160), (130, 129), (288, 480), (512, 512)])
 @pytest.mark.parametrize("M,p0", [(16, 0), (17, 47), (15, 63), (33, 500), (1, 511), (40, 1030)])
 def test_prefill_tiles(r_k, r_v, M, p0):
-    log(f"prefill fp32 tiles r=({r_k},{r_v}) M={M} p0={p0}")
-    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(SMALL, r_k, r_v, 1, M, p0, F32)
+    if r_v <= 256 and M < 16:
+        M += 32  # the same edges with queries enough for the matrix kernel
+    if r_v <= 32:
+        M = max(M, 32) + M % 16
+    wl = W.Workload("f32_tiles", 1, _heads(M, r_v), 128, 4, 1, 0, ((r_k, r_v),), F32)
+    log(f"prefill fp32 tiles r=({r_k},{r_v}) H={wl.H} M={M} p0={p0}")
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, p0, F32)
     out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
     assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, p0), F32, "prefill fp32")
 
 
+def _two_per_unit(B, H, M):
+    """More workgroups than compute units: below r_v = 256 two of them share one."""
+    return B * H * ((M + 15) // 16) > torch.cuda.get_device_properties(0).multi_processor_count
+
+
 @pytest.mark.parametrize("d_head", [32, 96, 256])
-def test_prefill_head_widths(d_head):
-    wl = W.Workload("f32_width", 1, 2, d_head, 4, 1, 0, ((36, 60),), F32)
+@pytest.mark.parametrize("H", [28, 100])
+def test_prefill_head_widths(H, d_head):
+    wl = W.Workload("f32_width", 1, H, d_head, 4, 1, 0, ((36, 60),), F32)
+    assert _heads(37, 60) <= 35 and _two_per_unit(1, H, 37) == (H == 100)
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, 36, 60, 1, 37, 70, F32)
     out = lla.prefill_attn(q, pk, pv, uk, uv, p0=70, mu_k=muk, mu_v=muv, out_dtype=F32)
     assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, 70), F32, f"d={d_head}")
 
 
+@pytest.mark.parametrize("H", [12, 44])
 @pytest.mark.parametrize("axis", ["k", "v"])
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
 @pytest.mark.parametrize("n_bad", [3, 63, 64, 70, 79])
-def test_nonfinite_reaches_only_its_queries(axis, value, n_bad):
+def test_nonfinite_reaches_only_its_queries(H, axis, value, n_bad):
     """A non-finite latent at position n makes queries n .. non-finite (a value
     latent; a key latent at least where its score is not -inf) and leaves the
     queries before n as they are."""
     r_k, r_v, M = 36, 60, 90
-    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(SMALL, r_k, r_v, 1, M, 0, F32)
+    wl = W.Workload("f32_nonfinite", 1, H, 128, 4, 1, 0, ((r_k, r_v),), F32)
+    assert lla.lib().lla_internal_f32_matrix_prefill(1, H, M, r_v) and _two_per_unit(1, H, M) == (H == 44)
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, 0, F32)
     ref = _oracle(q, ck, cv, uk, uv, muk, muv, 0)
     cache = pk if axis == "k" else pv
     cache[0, 1, n_bad // 64, 5, n_bad % 64] = value
