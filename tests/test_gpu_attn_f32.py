@@ -41,6 +41,40 @@ def _two_per_unit(B, H, M):
     return B * H * ((M + 15) // 16) > torch.cuda.get_device_properties(0).multi_processor_count
 
 
+@pytest.mark.parametrize("r_k,r_v", [(18, 30), (33, 17), (96, 160), (130, 129), (250, 256), (64, 128)])
+@pytest.mark.parametrize("M,p0", [(300, 37), (511, 0)])
+def test_prefill_many_tiles(r_k, r_v, M, p0):
+    """The variant for more workgroups than compute units, with one and two value
+    tiles per wavefront."""
+    wl = W.Workload("f32_many", 1, 16, 128, 4, 1, 0, ((r_k, r_v),), F32)
+    assert _two_per_unit(1, 16, M) and _heads(M, r_v) <= 16
+    log(f"prefill fp32 many tiles r=({r_k},{r_v}) M={M} p0={p0}")
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, p0, F32)
+    out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
+    assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, p0), F32, "prefill fp32")
+
+
+@pytest.mark.parametrize("Hr", [1, 16])
+@pytest.mark.parametrize("M", [100, 290])
+def test_prefill_rotary(Hr, M):
+    """The rotary rows, unwritten slots NaN, in both variants."""
+    wl = W.Workload("f32_rotary", 1, 16, 128, 4, 1, 0, ((36, 60),), F32)
+    r_k, r_v, dr, p0 = 36, 60, 40, 21
+    N = p0 + M
+    n_max = (N + 63) // 64 * 64 + 64
+    assert _two_per_unit(1, 16, M) == (M == 290) and _heads(M, r_v) <= 16
+    q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, p0, F32, n_max=n_max)
+    kr = W.rotary_keys(wl, dr, Hr, 0, B=1, N=N, device=DEV, dtype=F32)
+    qr = W.rotary_queries(wl, dr, 0, 2, B=1, M=M, device=DEV, dtype=F32)
+    rc = torch.full((1, Hr, n_max // 64, dr, 64), float("nan"), dtype=F32, device=DEV)
+    lla.rope_write(kr, rc, pos0=0)
+    log(f"prefill fp32 rotary Hr={Hr} M={M}")
+    out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv, q_rope=lla.rope_rotate(qr, pos0=p0), r_cache=rc)
+    ref = oracle.prefill_attn_rope_batched(f64(q), f64(qr), f64(ck), f64(cv), f64(kr).transpose(0, 2, 1, 3), f64(uk),
+                                           f64(uv), f64(muk), f64(muv), p0=p0)
+    assert_close(f64(out), ref, F32, "prefill fp32 rotary")
+
+
 @pytest.mark.parametrize("d_head", [32, 96, 256])
 @pytest.mark.parametrize("H", [28, 100])
 def test_prefill_head_widths(H, d_head):
