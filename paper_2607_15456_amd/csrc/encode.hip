@@ -727,17 +727,17 @@ __global__ __launch_bounds__(256) void encode_reduce_kernel(EncodeArgs a, int nr
 // straight from memory.  The four partial blocks add
 // through LDS in wavefront order, and a row of 32 tokens leaves as 128
 // consecutive bytes.  x - mu is formed in fp32 before the product.
-// grid: x = token block x row block (axis k, then v), y = head; a head's
+// grid: x = token block (from tb0) x row block (axis k, then v), y = head; a head's
 // workgroups on one XCD, whose L2 then holds its weights.  500 tokens of 16
 // heads, K = 512, (96, 160): 159 us with LDS-staged vector products (two LDS
 // reads per multiply-add), 37 us here (14 us of products at the matrix rate).
 constexpr int kFS = 36;  // LDS row stride of a partial block
-__global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a, int nrc_k, int nrc) {
+__global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a, int nrc_k, int nrc, int tb0) {
   __shared__ __attribute__((aligned(16))) float s_part[4][32 * kFS];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   int bx, h;
   xcd_head_order(bx, h, true);
-  const int tb = (unsigned)bx / (unsigned)nrc, rc_ = bx - tb * nrc;
+  const int tbl = (unsigned)bx / (unsigned)nrc, tb = tb0 + tbl, rc_ = bx - tbl * nrc;
   const int axis = rc_ >= nrc_k ? 1 : 0, rc = rc_ - axis * nrc_k;
   const int r = pick(a.r, axis), K = a.K, H = a.H, TT = a.B * a.M;
   const int c = lane & 15, g = lane >> 4;
@@ -885,9 +885,15 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
   const int rmax = a.r[0] > a.r[1] ? a.r[0] : a.r[1];
   const int nrc_k = (a.r[0] + 31) / 32, nrc_v = (a.r[1] + 31) / 32;
   if (a.dtype == LLA_F32) {
-    dim3 grid((TT + 31) / 32 * (nrc_k + nrc_v), a.H);
-    hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, a, nrc_k, nrc_k + nrc_v);
-    return hipGetLastError();
+    // a launch takes fewer than 2^32 threads along x: 2^24 - 1 workgroups
+    const int nb = (TT + 31) / 32, nrc = nrc_k + nrc_v, most = ((1 << 24) - 1) / nrc;
+    hipError_t e = hipSuccess;
+    for (int tb0 = 0; tb0 < nb && e == hipSuccess; tb0 += most) {
+      dim3 grid(std::min(most, nb - tb0) * nrc, a.H);
+      hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, a, nrc_k, nrc, tb0);
+      e = hipGetLastError();
+    }
+    return e;
   }
   const int blocks = (TT + kEncTok - 1) / kEncTok;
   switch (bf16_route(a)) {
