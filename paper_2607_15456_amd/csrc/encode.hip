@@ -16,6 +16,7 @@
 // fp32: the same product on the fp32 matrix instructions, 32 x 32 tiles.
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "lla_device.h"
@@ -799,7 +800,7 @@ struct GemmGrid {
   int nrb_k, nrb;  // row blocks of axis k, of both axes
   int nsb, ntb;    // token blocks per sequence (0: of the flattened tokens), in all
   int hpw;         // heads per workgroup
-  int rounds;      // workgroups that one slot of the busiest XCD takes in turn (two slots per compute unit)
+  double rounds;   // workgroups that a slot of the busiest XCD takes in turn (two slots per compute unit)
   explicit GemmGrid(const EncodeArgs& a) {
     const int TT = a.B * a.M, q = 128 * XT;
     nrb_k = (a.r[0] + kGRow - 1) / kGRow;
@@ -817,34 +818,39 @@ struct GemmGrid {
     // writes) do not pay the pipeline fill per head; 32 are for few workgroups.
     hpw = 1;
     if (XT == 2) hpw = (int)std::min<int64_t>(a.H, std::max<int64_t>(1, (int64_t)a.H * nrb * ntb / 2048));
-    const int64_t per_xcd = (int64_t)((ntb + 7) / 8) * nrb * a.H, slots = std::max(1, device_cu_count() / 4);
-    rounds = (int)((per_xcd + slots - 1) / slots);
+    // whole rounds while they are few, then half a round of slack
+    rounds = (double)((ntb + 7) / 8) * nrb * a.H / std::max(1, device_cu_count() / 4);
+    rounds = rounds < 3 ? std::ceil(rounds) : rounds + 0.5;
   }
 };
 
 // Whether a bf16 write of more than 64 tokens runs the GEMM rather than the
-// 32-token kernel.  A GEMM workgroup takes longer and does more, so it pays where
-// the 32-token kernel's workgroups (tokens / 32 x heads x row chunks of both
-// axes) come in several rounds: from about 900 at K = 512, more the shorter K is.
-// The line was drawn, and checked, over 3000 writes of 1 to 32 heads, K 64 to 2048,
-// ranks 1 to 512 and 65 to 40,000 tokens: the kernel turned down is faster by more
-// than 3% in one of 200, and nowhere with 16 heads and K = 512.  32-token kernel / GEMM: 300 tokens of 16 heads (96, 160) at K = 512 24.4 / 20.1 us, of 4 heads
-// (203 tokens) 8.4 / 14.6; (36, 60) 3000 tokens of 16 heads 75.7 / 26.4, 1532 of 2
-// heads 10.2 / 13.6.  Below 256 tokens its blocks are largely padding (195
-// tokens (192, 320) 24.6 / 28.0, 200 (288, 480) 41.5 / 29.5), the more so for
-// short sequences (32 of 7, 32 heads, K = 192 33.8 / 38.5).  Stacks of 2048
-// values and more (LLA-2D) gain from 256 tokens.
+// 32-token kernel.  A GEMM workgroup takes longer and does more (the more, the
+// fuller its row blocks), so it pays where the 32-token kernel's workgroups
+// (tokens / 32 x heads x 32-row tiles) come in several rounds: from about 640 at K
+// = 512 and row blocks of 2.5 tiles, more the shorter K is; the 32-token kernel
+// multiplies a mean once more, the GEMM nearly for free.  The line was drawn over
+// 3871 writes of 1 to 32 heads, K 64 to 2048, ranks 1 to 512 and 192 to 40,000
+// tokens, every kernel timed on each, with repeated and with other inputs: the one chosen
+// is within 4% of the best of the three in 95 of 100, within 10% in 99.  32-token
+// kernel / GEMM, 16 heads, K = 512: 300 tokens (96, 160) 24.4 / 20.1 us, 651 tokens (18, 30)
+// 13.1 / 8.5, 3000 tokens (36, 60) 75.7 / 26.4; 4 heads, 203 tokens (96, 160) 8.4 / 14.6;
+// 2 heads, 1532 tokens (36, 60) 10.2 / 13.6.  Below 256 tokens a token block is
+// largely padding (2 x 98 tokens (120, 200) 22.3 / 24.0, 197 (288, 480) 43.6 /
+// 31.2).  Stacks of 2048 values and more (LLA-2D) gain from 256 tokens.
 bool gemm_ok(const EncodeArgs& a) {
-  const int TT = a.B * a.M, rmax = a.r[0] > a.r[1] ? a.r[0] : a.r[1];
+  const int TT = a.B * a.M, nt = (a.r[0] + 31) / 32 + (a.r[1] + 31) / 32, nrb = GemmGrid<1>(a).nrb;
   if (TT < 192 || a.K % kGKC) return false;
-  const int64_t work = (int64_t)((TT + kEncTok - 1) / kEncTok) * a.H * 2 * ((rmax + 31) / 32) * (a.K + 512);
-  if (TT < 256) return a.K < 2048 && rmax > 64 && a.M >= 64 && work > 3 << 20;
-  return a.K >= 2048 || work > 900 << 10;
+  if (a.K >= 2048 && TT >= 256) return true;
+  const double mean = a.mu[0] || a.mu[1] ? 1.375 : 1.0;
+  const double work = (double)((TT + kEncTok - 1) / kEncTok) * a.H * nt * (a.K + 576) * mean * nrb / (nrb + nt);
+  return work > (TT < 256 ? 486 << 10 : 195 << 10);
 }
 
-// 64 tokens per wavefront where 32 take more than 1.7 times the rounds (a
-// workgroup of 64 takes 1.7 times as long as one of 32), else 32.
-bool gemm_wide(const EncodeArgs& a) { return 17 * (int64_t)GemmGrid<2>(a).rounds < 10 * (int64_t)GemmGrid<1>(a).rounds; }
+// 64 tokens per wavefront where 32 take more than 1.63 times the rounds (a
+// workgroup of 64 takes that much longer), else 32: 1800 tokens of 16 heads (240, 400)
+// with means 60 us with 32, 88 with 64 in the same number of rounds.
+bool gemm_wide(const EncodeArgs& a) { return 1.63 * GemmGrid<2>(a).rounds < GemmGrid<1>(a).rounds; }
 
 // The kernel of a bf16 write.
 enum Route { kFew, kStream, kTok32, kGemm1, kGemm2 };
@@ -921,7 +927,7 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
     case kTok32: break;
   }
   // One head and two row tiles per workgroup, so that the weights spread over
-  // the machine; of 8192 tokens and more (few heads, or K an odd multiple of 32)
+  // the machine; of 8192 tokens and more (mostly K an odd multiple of 32)
   // all heads of its 32 tokens, one contiguous region of x.
   const int heads_per_wg = blocks >= 256 ? a.H : 1;
   const int rtmax = (rmax + 15) / 16;
@@ -935,9 +941,9 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
 }  // namespace lla
 
 // Kernel of a bf16 write (enum Route), and of a GEMM write its heads per
-// workgroup, token blocks and rounds.
-extern "C" int lla_internal_encode_route(int B, int M, int H, int K, int r_k, int r_v, int pos0, int* heads,
-                                         int* blocks, int* rounds) {
+// workgroup and token blocks.
+extern "C" int lla_internal_encode_route(int B, int M, int H, int K, int r_k, int r_v, int means, int pos0,
+                                         int* heads, int* blocks) {
   lla::EncodeArgs a{};
   a.dtype = LLA_BF16;
   a.B = B;
@@ -946,13 +952,13 @@ extern "C" int lla_internal_encode_route(int B, int M, int H, int K, int r_k, in
   a.K = K;
   a.r[0] = r_k;
   a.r[1] = r_v;
+  a.mu[0] = means ? &a : nullptr;
   a.pos0 = pos0;
   const lla::Route route = lla::bf16_route(a);
-  *heads = *blocks = *rounds = 0;
+  *heads = *blocks = 0;
   auto fill = [&](const auto& g) {
     *heads = g.hpw;
     *blocks = g.ntb;
-    *rounds = g.rounds;
   };
   if (route == lla::kGemm1) fill(lla::GemmGrid<1>(a));
   if (route == lla::kGemm2) fill(lla::GemmGrid<2>(a));

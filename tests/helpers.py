@@ -77,9 +77,9 @@ def assert_units_close(got, ref, what=""):
 FEW, STREAM, TOK32, GEMM1, GEMM2 = range(5)
 
 
-def encode_route(lib, B, M, H, K, r_k, r_v, pos0=0):
-    """(kernel, heads per workgroup, token blocks, rounds) that the library
-    chooses for a bf16 write."""
-    out = [ctypes.c_int() for _ in range(3)]
-    return (lib.lla_internal_encode_route(B, M, H, K, r_k, r_v, pos0, *map(ctypes.byref, out)),
+def encode_route(lib, B, M, H, K, r_k, r_v, pos0=0, means=False):
+    """(kernel, heads per workgroup, token blocks) that the library chooses for
+    a bf16 write."""
+    out = [ctypes.c_int() for _ in range(2)]
+    return (lib.lla_internal_encode_route(B, M, H, K, r_k, r_v, int(means), pos0, *map(ctypes.byref, out)),
             *(o.value for o in out))

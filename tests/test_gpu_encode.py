@@ -153,14 +153,13 @@ def test_encode_many_tokens(r_k, r_v, T, d, B, M, pos0):
 @pytest.mark.parametrize("r_k,r_v,T,d,H,B,M,pos0", [
     (33, 17, 1, 96, 3, 1, 8200, 60),   # K an odd multiple of 32
     (150, 40, 3, 32, 2, 3, 2800, 5),   # more than 8 row tiles: two chunks of them
-    (8, 30, 1, 64, 1, 2, 4100, 1),     # too little work for the GEMM
 ])
 def test_encode_many_tokens_32(r_k, r_v, T, d, H, B, M, pos0):
     """Writes of 8192 tokens and more on the 32-token kernel: a workgroup takes
     all heads of its tokens."""
     wl = W.Workload(f"enc_many32_{T}_{d}", 1, H, d, T, B, 0, ((r_k, r_v),), torch.bfloat16)
     n_max = ((pos0 + M + 63) // 64) * 64 + 64
-    assert encode_route(lla.lib(), B, M, H, T * d, r_k, r_v, pos0)[0] == TOK32
+    assert encode_route(lla.lib(), B, M, H, T * d, r_k, r_v, pos0, True)[0] == TOK32
     log(f"encode many tokens r=({r_k},{r_v}) K={T * d} H={H} B={B} M={M} pos0={pos0}")
     inputs, ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, True, torch.bfloat16)
     _check(wl, inputs, ck, cv, pos0, M, torch.bfloat16, f"M={M}")
@@ -177,7 +176,7 @@ def test_encode_many_tokens_32(r_k, r_v, T, d, H, B, M, pos0):
 def test_encode_many_tokens_tier_ranks(r_k, r_v, T, d, B, M, pos0, means):
     """Prompt-sized writes at the paper's per-head rank tiers: the MFMA GEMM path."""
     wl = W.Workload(f"enc_tier_{T}_{d}", 1, 8, d, T, B, 0, ((r_k, r_v),), torch.bfloat16)
-    assert encode_route(lla.lib(), B, M, wl.H, T * d, r_k, r_v, pos0)[0] in (GEMM1, GEMM2)
+    assert encode_route(lla.lib(), B, M, wl.H, T * d, r_k, r_v, pos0, means)[0] in (GEMM1, GEMM2)
     n_max = ((pos0 + M + 63) // 64) * 64 + 64
     log(f"encode tier ranks r=({r_k},{r_v}) K={T * d} B={B} M={M} pos0={pos0} means={means}")
     inputs, ck, cv = _run(wl, r_k, r_v, B, M, pos0, n_max, means, torch.bfloat16)
@@ -196,7 +195,7 @@ def test_encode_gemm_head_runs(r_k, r_v, T, d, H, B, M, pos0, runs, means):
     """Prompt-sized per-head writes where a GEMM workgroup walks a run of heads,
     over odd and even chunk counts and including a last run shorter than the
     others; every latent is checked against the oracle."""
-    route, heads, _, _ = encode_route(lla.lib(), B, M, H, T * d, r_k, r_v, pos0)
+    route, heads, _ = encode_route(lla.lib(), B, M, H, T * d, r_k, r_v, pos0, means)
     assert (route, heads) == (GEMM2 if runs > 1 else GEMM1, runs), "case no longer takes the intended runs"
     wl = W.Workload(f"enc_runs_{T}_{d}_{H}", 1, H, d, T, B, 0, ((r_k, r_v),), torch.bfloat16)
     n_max = ((pos0 + M + 63) // 64) * 64 + 64
@@ -212,7 +211,7 @@ def test_encode_gemm_ring_slots(r_k, r_v, means):
     holds the oracle's latent of that token (later tokens overwrite earlier ones)."""
     sink, window, chunks = 4, 512, [300, 500, 260]  # at most `window` tokens per call
     wl = W.Workload("enc_ring_gemm", 1, 8, 128, 4, 2, 0, ((r_k, r_v),), torch.bfloat16)
-    assert all(encode_route(lla.lib(), 2, m, 8, 512, r_k, r_v)[0] in (GEMM1, GEMM2) for m in chunks)
+    assert all(encode_route(lla.lib(), 2, m, 8, 512, r_k, r_v, 0, means)[0] in (GEMM1, GEMM2) for m in chunks)
     B, H, K = wl.B, wl.H, wl.T * wl.d
     n_max = ((sink + window + 63) // 64) * 64
     wk = W.down_projection(wl, r_k, "k", 0, DEV, torch.bfloat16)
@@ -264,7 +263,7 @@ def test_gemm_tiles(r_k, r_v, B, M, pos0, T, d_head, means):
         M = 257  # the fewest tokens that take the GEMM at these ranks
     want = GEMM2 if M == 1997 else GEMM1
     H = next(h for h in (3, 5, 9, 17, 33, 48, 65, 97, 129, 193)
-             if encode_route(lla.lib(), B, M, h, T * d_head, r_k, r_v, pos0)[0] == want)
+             if encode_route(lla.lib(), B, M, h, T * d_head, r_k, r_v, pos0, means)[0] == want)
     wl = W.Workload("enc_gemm", 1, H, d_head, T, B, 0, ((18, 30),), torch.bfloat16)
     n_max = (pos0 + M + 63) // 64 * 64 + 64
     log(f"encode gemm r=({r_k},{r_v}) B={B} M={M} pos0={pos0} H={H} K={T * d_head} means={means}")
