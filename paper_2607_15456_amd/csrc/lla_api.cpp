@@ -99,50 +99,59 @@ int f32_slices(int units, int pages, bool allow_split) {
 }
 
 // fp32 decode: the matrix kernel (one 8-wavefront workgroup per slice, a page per
-// wavefront, the 16-row value tiles dealt over the wavefronts) or the scan.  Drawn
-// from 1350 calls (1 to 2048 units, 1 to 9000 tokens, ranks 1 to 512, d_head 32 to
-// 256, repeated and with other inputs between); the choice is nowhere more than 3%
-// slower than the scan.  One call, scan / matrix, repeated inputs:
-//  - r_v > 256, where the scan's rows no longer fit its registers: the matrix
-//    kernel ((288, 480) 1 token 101 / 33 us, 2500 tokens of 128 units 581 / 222),
-//    but one workgroup does not walk more than 32 pages alone while compute units
-//    are idle ((192, 320) 3912 tokens of 32 units, no workspace 267 / 306), nor
-//    one page for more than two of them per unit ((192, 320) 114 / 132).
-//  - 64 < r_v <= 256 over few units: where slices keep it at 16 pages at most ((96,
-//    160) 1573 tokens 54 / 32, (48, 80) and up), and above 128 also a single group
-//    of 8 pages (512 tokens 26 / 24; 858 tokens in one slice 33 / 40).  A r_v that is
-//    not a multiple of 4 reads U_v by the element ((80, 130) 1 token 18 / 19).
-//  - r_v <= 64: half of the wavefronts and more have no value tile ((64, 64) 1
-//    token 10.9 / 12.0, (36, 60) 3756 tokens without a workspace 21 / 61).
-// Contexts of 64 pages and more over few units keep the scan's split counts, which
-// lla_decode_splits reports.
-bool f32_matrix_decode(int units, int pages, int slices, int r_v) {
+// wavefront, the 16-row value tiles dealt over the wavefronts) or the scan, for
+// contexts below 64 pages of few units and for r_v > 256 (others keep the scan and
+// its split counts, which lla_decode_splits reports).  The lines were drawn over
+// 1939 such calls (1 to 2048 units, 1 to 9000 tokens, ranks 1 to 512, d_head 32 to
+// 256, both kernels timed on each, with repeated and with other inputs): the one chosen is
+// 0.35% slower than the better one on average, by more than 10% in 16.  One call,
+// scan / matrix, repeated inputs:
+//  - r_v > 176: the scan's rows do not fit its registers ((288, 480) 1 token 101 / 33
+//    us, (120, 200) 1578 tokens of one unit 94 / 40); but several single pages per
+//    compute unit below r_v = 400 ((192, 320) 1024 units 114 / 132).
+//  - unsplit, one group of 8 pages at most ((96, 160) 512 tokens 26 / 24, 858 tokens
+//    33 / 40; (64, 64) 935 tokens 14 / 22); split, slices of 18 pages at most ((96,
+//    160) 1573 tokens 54 / 32; 4 x 3928 tokens 97 / 60), below r_v = 88 two slices of 11
+//    or more slices ((36, 60) 3059 tokens 34 / 20; (36, 60) 1712 tokens in 3 with the
+//    rotary branch 24 / 30).
+//  - small products, where the prologue and epilogue over d_head count: r_v <= 88 at
+//    d_head 256 ((64, 64) 21 tokens 14 / 18) or one page with the rotary branch ((36, 60)
+//    11.9 / 13.5); a r_v that is not a multiple of 4, whose U_v is read by the
+//    element, over one or two pages ((80, 130) 18.1 / 19.4).
+bool f32_matrix_decode(int units, int pages, int slices, int r_v, int d_head, int d_rope) {
   const int cus = lla::device_cu_count(), per = (pages + slices - 1) / slices;
-  if (r_v > 256) return units >= cus ? pages >= 2 || units <= 2 * cus : pages < 64 && per <= 32;
-  if (r_v <= 64 || r_v % 4 || pages >= 64 || 2 * units > cus) return false;
-  return slices > 1 ? per <= 16 : r_v > 128 && per <= 8;
+  if (r_v > 256 ? pages >= 64 && units < cus : r_v <= 32 || pages >= 64 || 2 * units > cus) return false;
+  if (r_v > 176) return pages > 1 || units <= 2 * cus || r_v >= 400;
+  if (r_v <= 88 && pages < 16 && (d_head > 192 || (d_rope && pages == 1))) return false;
+  if (r_v > 88 && r_v % 4 && pages <= 2 && 4 * units <= cus) return false;
+  if (slices == 1) return per <= 8;
+  return r_v > 88 ? per <= 18 : slices > 2 || per <= 11;
 }
 
 // fp32 prefill: the matrix kernel takes 16 queries of a unit per workgroup, the scan
 // one.  Few queries in all run side by side in the scan, whose workgroups are the
-// shorter ones, so below 1024 queries over all units (four workgroups per compute
-// unit) the matrix kernel is kept for ranks where a tile costs less than the
-// scan's slowest query; drawn from 1350 calls (1 to 1024 units, 1 to 700 queries
-// after up to 4000 keys, ranks 1 to 512, d_head 32 to 256, repeated and with other
-// inputs between), one of which is slower than the scan by 8%.  One call, scan /
-// matrix: 500 queries of 16 heads (96, 160) 305 / 38 us, 431 of 256 units (16, 16)
-// 844 / 200; 350 queries of one head after 3729 keys (65, 33) 55 / 86, 59 of 4
-// units after 3270 (8, 8) 14 / 42; 16 queries of 16 heads (96, 160) after 2000
-// keys 85 / 78, at (18, 30) 24 / 29 (32 from there on); r_v > 256, one query after
-// 8000 keys 1412 / 753.
-bool f32_matrix_prefill(int units, int M, int r_v) {
+// shorter ones; with r_v the scan's cost grows, so the line is on queries x r_v over
+// all units.  Below it the matrix kernel keeps calls over one group of 8 pages at
+// ranks that occupy its wavefronts.  Drawn over 2490 calls (1 to 1024 units, 1 to 700
+// queries after up to 4000 keys, ranks 1 to 512, d_head 32 to 256, both timed with
+// repeated and with other inputs): 0.3% slower than the better one on average, by more than
+// 10% in 30.  One call, scan / matrix: 500 queries of 16 heads (96, 160) 305 / 38
+// us, 431 of 256 units (16, 16) 844 / 200; 350 of one head after 3729 keys (65, 33)
+// 55 / 86, 59 of 4 units after 3270 (8, 8) 14 / 42; 4 of 128 units after 73 keys
+// (120, 200) 48 / 20; 16 of 16 heads after 2000 keys (96, 160) 85 / 78, (18, 30)
+// 24 / 29; r_v > 256, one query after 8000 keys 1412 / 753.
+bool f32_matrix_prefill(int units, int M, int keys, int r_v, int d_head, int d_rope) {
+  const int cus = lla::device_cu_count();
   if (r_v > 256) return true;
-  if (M < 16) return false;
-  if (r_v > 128 && r_v % 4 == 0) return true;
-  return (int64_t)units * M >= 4 * lla::device_cu_count() && (M >= 32 || r_v > 32);
+  if (M < (r_v > 32 ? 16 : 32) && (keys > 512 || 2 * units > cus)) return false;
+  if ((int64_t)units * M * r_v > 47LL * cus) return true;
+  if (r_v <= 32 || keys > 512) return false;
+  return r_v > 88 || (d_head <= 192 && !(d_rope && keys <= 64));
 }
 
-DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int row_blocks, int r_v) {
+// d_head: not what the split count of any shape depends on.
+DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int row_blocks, int r_v, int d_rope,
+                         int d_head = 128) {
   static const int forced_waves = env_int("LLA_DECODE_WAVES");
   static const int forced_splits = env_int("LLA_DECODE_SPLITS");
   static const int forced_deep = env_int("LLA_DECODE_DEEP");
@@ -153,7 +162,7 @@ DecodeShape choose_shape(int units, int n_ctx, bool allow_split, bool bf16, int 
   const int pages = (n_ctx + LLA_PAGE_TOKENS - 1) / LLA_PAGE_TOKENS;
   const int groups = (pages + 7) / 8;
   const int slices = f32_slices(units, pages, allow_split);
-  if (!bf16 && !forced_waves && f32_matrix_decode(units, pages, slices, r_v)) {
+  if (!bf16 && !forced_waves && f32_matrix_decode(units, pages, slices, r_v, d_head, d_rope)) {
     const bool forced = forced_splits > 0 && allow_split;
     return DecodeShape{8, forced ? std::min(forced_splits, max_splits(n_ctx)) : slices, 0, 0, 0, 1};
   }
@@ -285,12 +294,14 @@ double lla_internal_rope_frequency(double base, double c) {
 }
 
 // Whether an fp32 decode takes the matrix kernel.
-int lla_internal_f32_matrix_decode(int B, int H, int n_ctx, int r_v, int with_workspace) {
-  return choose_shape(B * H, n_ctx, with_workspace != 0, false, 1, r_v).matrix;
+int lla_internal_f32_matrix_decode(int B, int H, int n_ctx, int r_v, int d_head, int d_rope, int with_workspace) {
+  return choose_shape(B * H, n_ctx, with_workspace != 0, false, 1, r_v, d_rope, d_head).matrix;
 }
 
 // Whether an fp32 prefill takes the matrix kernel.
-int lla_internal_f32_matrix_prefill(int B, int H, int M, int r_v) { return f32_matrix_prefill(B * H, M, r_v); }
+int lla_internal_f32_matrix_prefill(int B, int H, int M, int p0, int r_v, int d_head, int d_rope) {
+  return f32_matrix_prefill(B * H, M, p0 + M, r_v, d_head, d_rope);
+}
 
 const char* lla_status_string(int status) {
   switch (status) {
@@ -441,7 +452,7 @@ lla_status lla_decode_splits(int dtype, int B, int H, int n_ctx, int r_k, int r_
       !rank_ok(r_k) || !rank_ok(r_v) || d_rope < 0 || d_rope > LLA_MAX_ROPE)
     return LLA_ERR_INVALID_ARG;
   *splits = choose_shape(B * H, n_ctx, with_workspace != 0, dtype == LLA_BF16,
-                         row_blocks_of(r_k, r_v, d_rope), r_v).splits;
+                         row_blocks_of(r_k, r_v, d_rope), r_v, d_rope).splits;
   return LLA_OK;
 }
 
@@ -534,7 +545,7 @@ lla_status decode_impl(int dtype, int out_dtype, int B, int H, int d_head, int r
   a.qr = q_rope;
   a.rc = r_cache;
   const DecodeShape sh = choose_shape(B * H, n_ctx, static_scratch || workspace != nullptr,
-                                      dtype == LLA_BF16, row_blocks_of(r_k, r_v, d_rope), r_v);
+                                      dtype == LLA_BF16, row_blocks_of(r_k, r_v, d_rope), r_v, d_rope, d_head);
   a.waves = sh.waves;
   a.splits = sh.splits;
   a.deep = sh.deep;
@@ -777,7 +788,7 @@ lla_status prefill_impl(int dtype, int out_dtype, int B, int H, int M, int d_hea
   a.splits = 1;
   a.waves = 4;
   a.deep = 0;
-  a.matrix = f32_matrix_prefill(B * H, M, r_v) ? 1 : 0;
+  a.matrix = f32_matrix_prefill(B * H, M, p0 + M, r_v, d_head, d_rope) ? 1 : 0;
   a.q = q;
   a.ck = c_k;
   a.cv = c_v;

@@ -195,6 +195,6 @@ double lla_internal_rope_frequency(double base, double c);
 int lla_internal_encode_route(int B, int M, int H, int K, int r_k, int r_v, int means, int pos0, int* heads,
                               int* blocks);
 int lla_internal_key_streams(int B, int H, int M, int p0);
-int lla_internal_f32_matrix_decode(int B, int H, int n_ctx, int r_v, int with_workspace);
-int lla_internal_f32_matrix_prefill(int B, int H, int M, int r_v);
+int lla_internal_f32_matrix_decode(int B, int H, int n_ctx, int r_v, int d_head, int d_rope, int with_workspace);
+int lla_internal_f32_matrix_prefill(int B, int H, int M, int p0, int r_v, int d_head, int d_rope);
 }

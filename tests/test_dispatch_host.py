@@ -5,6 +5,7 @@ import ctypes
 import decimal
 
 import pytest
+import torch
 
 from paper_2607_15456_amd import lla
 from tests.helpers import FEW, GEMM1, GEMM2, STREAM, TOK32, encode_route
@@ -99,42 +100,60 @@ def test_key_streams_grid(host):
         assert streams in (1, 2, 4, 8) and -(-M // (256 // streams)) <= 65535
 
 
-@pytest.mark.parametrize("B,H,n_ctx,r_v,workspace,matrix", [
+@pytest.mark.parametrize("B,H,n_ctx,r_v,d_head,d_rope,workspace,matrix", [
     # us, scan / matrix
-    (1, 16, 512, 160, 1, 1),      # 26 / 24
-    (1, 16, 858, 160, 1, 0),      # 33 / 40
-    (1, 4, 1573, 160, 1, 1),      # 54 / 32
-    (1, 16, 2833, 160, 0, 0),     # 106 / 133
-    (1, 16, 8000, 160, 1, 0),
-    (16, 16, 512, 160, 1, 0),
-    (1, 16, 1, 64, 1, 0),         # 10.9 / 12.0
-    (1, 16, 3756, 60, 0, 0),      # 21 / 61
-    (1, 16, 1500, 128, 1, 1),
-    (1, 16, 1500, 128, 0, 0),
-    (1, 8, 4, 130, 1, 0),         # 18 / 20
-    (1, 16, 1, 480, 1, 1),        # 101 / 33
-    (8, 16, 2551, 480, 1, 1),     # 581 / 222
-    (1, 32, 3912, 320, 0, 0),     # 267 / 306
-    (32, 32, 6, 320, 1, 0),       # 114 / 132
-    (64, 16, 2048, 320, 1, 1),
+    (1, 16, 512, 160, 128, 0, 1, 1),      # 26 / 24
+    (1, 16, 858, 160, 128, 0, 1, 0),      # 33 / 40
+    (1, 4, 1573, 160, 128, 0, 1, 1),      # 54 / 32
+    (1, 16, 2833, 160, 128, 0, 0, 0),     # 106 / 133
+    (4, 16, 3928, 160, 128, 0, 1, 1),     # 97 / 60
+    (1, 16, 8000, 160, 128, 0, 1, 0),
+    (16, 16, 512, 160, 128, 0, 1, 0),
+    (1, 16, 3756, 60, 128, 0, 0, 0),      # 21 / 61
+    (2, 4, 3059, 60, 128, 0, 1, 1),       # 34 / 20
+    (4, 2, 935, 64, 128, 0, 0, 0),        # 14 / 22
+    (1, 2, 21, 64, 256, 0, 1, 0),         # 14 / 18
+    (1, 16, 1, 60, 128, 64, 1, 0),        # 11.9 / 13.5
+    (1, 16, 100, 30, 128, 0, 1, 0),
+    (1, 8, 4, 130, 128, 0, 1, 0),         # 18 / 20
+    (1, 1, 1978, 200, 128, 0, 1, 1),      # 94 / 40
+    (1, 16, 1, 480, 128, 0, 1, 1),        # 101 / 33
+    (8, 16, 2551, 480, 128, 0, 1, 1),     # 581 / 222
+    (32, 32, 6, 320, 128, 64, 1, 0),      # 114 / 132
+    (64, 16, 19, 480, 128, 0, 1, 1),      # 214 / 135
+    (64, 16, 2048, 320, 128, 0, 1, 1),
 ])
-def test_f32_decode(host, B, H, n_ctx, r_v, workspace, matrix):
-    assert host.lla_internal_f32_matrix_decode(B, H, n_ctx, r_v, workspace) == matrix
+def test_f32_decode(host, B, H, n_ctx, r_v, d_head, d_rope, workspace, matrix):
+    assert host.lla_internal_f32_matrix_decode(B, H, n_ctx, r_v, d_head, d_rope, workspace) == matrix
 
 
-@pytest.mark.parametrize("B,H,M,r_v,matrix", [
+def test_f32_decode_splits_without_head_width():
+    """lla_decode_splits does not know d_head: no split count may depend on it.
+    Where the choice of kernel does (below 16 pages) both take one slice."""
+    for r_v in (33, 60, 88):
+        for pages in range(1, 17):
+            for units in (1, 16, 128):
+                n = pages * 64
+                wide = lla.lib().lla_internal_f32_matrix_decode(1, units, n, r_v, 256, 0, 1)
+                narrow = lla.lib().lla_internal_f32_matrix_decode(1, units, n, r_v, 128, 0, 1)
+                if wide != narrow:
+                    assert pages < 16 and lla.decode_splits(torch.float32, 1, units, n, 30, r_v) == 1
+
+
+@pytest.mark.parametrize("B,H,M,p0,r_v,d_head,d_rope,matrix", [
     # us, scan / matrix
-    (1, 16, 500, 160, 1),    # 305 / 38
-    (32, 8, 431, 16, 1),     # 844 / 200
-    (1, 1, 350, 33, 0),      # 55 / 86, after 3729 keys
-    (2, 2, 59, 8, 0),        # 14 / 42, after 3270 keys
-    (1, 16, 64, 30, 1),      # 50 / 32, after 2000 keys
-    (1, 16, 63, 30, 0),
-    (64, 16, 31, 30, 0),
-    (1, 16, 16, 160, 1),     # 85 / 78, after 2000 keys
-    (4, 2, 13, 160, 0),      # 22 / 24
-    (1, 1, 38, 162, 0),      # not a multiple of 4
-    (1, 1, 1, 320, 1),
+    (1, 16, 500, 0, 160, 128, 0, 1),      # 305 / 38
+    (32, 8, 431, 271, 16, 128, 0, 1),     # 844 / 200
+    (1, 1, 350, 3729, 33, 128, 64, 0),    # 55 / 86
+    (2, 2, 59, 3270, 8, 128, 0, 0),       # 14 / 42
+    (1, 1, 40, 600, 160, 128, 0, 0),
+    (1, 16, 64, 2000, 30, 128, 0, 1),     # 50 / 32
+    (1, 16, 24, 2000, 30, 128, 0, 0),
+    (8, 16, 4, 73, 200, 128, 0, 1),       # 48 / 20
+    (1, 16, 16, 2000, 160, 128, 0, 1),    # 85 / 78
+    (1, 2, 18, 10, 33, 256, 0, 0),        # 16 / 21
+    (1, 4, 1, 8, 33, 128, 64, 0),         # 14 / 16
+    (1, 1, 1, 8000, 320, 128, 0, 1),
 ])
-def test_f32_prefill(host, B, H, M, r_v, matrix):
-    assert host.lla_internal_f32_matrix_prefill(B, H, M, r_v) == matrix
+def test_f32_prefill(host, B, H, M, p0, r_v, d_head, d_rope, matrix):
+    assert host.lla_internal_f32_matrix_prefill(B, H, M, p0, r_v, d_head, d_rope) == matrix

@@ -17,19 +17,20 @@ pytestmark = pytest.mark.gpu
 DEV, F32 = "cuda", torch.float32
 
 
-def _heads(M, r_v):
+def _heads(M, p0, r_v, d_head=128, d_rope=0):
     """The fewest of some head counts with which one sequence's M queries take the matrix kernel."""
-    return next(h for h in (3, 16, 35, 66) if lla.lib().lla_internal_f32_matrix_prefill(1, h, M, r_v))
+    return next(h for h in (3, 12, 16, 28, 35, 66, 130, 400, 800)
+                if lla.lib().lla_internal_f32_matrix_prefill(1, h, M, p0, r_v, d_head, d_rope))
 
 
 @pytest.mark.parametrize("r_k,r_v", [(18, 30), (33, 17), (1, 1), (96, 160), (130, 129), (288, 480), (512, 512)])
 @pytest.mark.parametrize("M,p0", [(16, 0), (17, 47), (15, 63), (33, 500), (1, 511), (40, 1030)])
 def test_prefill_tiles(r_k, r_v, M, p0):
-    if r_v <= 256 and M < 16:
+    if r_v <= 256 and M < 16 and p0 > 64:
         M += 32  # the same edges with queries enough for the matrix kernel
     if r_v <= 32:
-        M = max(M, 32) + M % 16
-    wl = W.Workload("f32_tiles", 1, _heads(M, r_v), 128, 4, 1, 0, ((r_k, r_v),), F32)
+        M = 256 + M
+    wl = W.Workload("f32_tiles", 1, _heads(M, p0, r_v), 128, 4, 1, 0, ((r_k, r_v),), F32)
     log(f"prefill fp32 tiles r=({r_k},{r_v}) H={wl.H} M={M} p0={p0}")
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, p0, F32)
     out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
@@ -47,7 +48,7 @@ def test_prefill_many_tiles(r_k, r_v, M, p0):
     """The variant for more workgroups than compute units, with one and two value
     tiles per wavefront."""
     wl = W.Workload("f32_many", 1, 16, 128, 4, 1, 0, ((r_k, r_v),), F32)
-    assert _two_per_unit(1, 16, M) and _heads(M, r_v) <= 16
+    assert _two_per_unit(1, 16, M) and _heads(M, p0, r_v) <= 16
     log(f"prefill fp32 many tiles r=({r_k},{r_v}) M={M} p0={p0}")
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, p0, F32)
     out = lla.prefill_attn(q, pk, pv, uk, uv, p0=p0, mu_k=muk, mu_v=muv)
@@ -62,7 +63,7 @@ def test_prefill_rotary(Hr, M):
     r_k, r_v, dr, p0 = 36, 60, 40, 21
     N = p0 + M
     n_max = (N + 63) // 64 * 64 + 64
-    assert _two_per_unit(1, 16, M) == (M == 290) and _heads(M, r_v) <= 16
+    assert _two_per_unit(1, 16, M) == (M == 290) and _heads(M, p0, r_v, d_rope=dr) <= 16
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, p0, F32, n_max=n_max)
     kr = W.rotary_keys(wl, dr, Hr, 0, B=1, N=N, device=DEV, dtype=F32)
     qr = W.rotary_queries(wl, dr, 0, 2, B=1, M=M, device=DEV, dtype=F32)
@@ -79,7 +80,7 @@ def test_prefill_rotary(Hr, M):
 @pytest.mark.parametrize("H", [28, 100])
 def test_prefill_head_widths(H, d_head):
     wl = W.Workload("f32_width", 1, H, d_head, 4, 1, 0, ((36, 60),), F32)
-    assert _heads(37, 60) <= 35 and _two_per_unit(1, H, 37) == (H == 100)
+    assert _heads(37, 70, 60, d_head) <= 28 and _two_per_unit(1, H, 37) == (H == 100)
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, 36, 60, 1, 37, 70, F32)
     out = lla.prefill_attn(q, pk, pv, uk, uv, p0=70, mu_k=muk, mu_v=muv, out_dtype=F32)
     assert_close(f64(out), _oracle(q, ck, cv, uk, uv, muk, muv, 70), F32, f"d={d_head}")
@@ -95,7 +96,7 @@ def test_nonfinite_reaches_only_its_queries(H, axis, value, n_bad):
     queries before n as they are."""
     r_k, r_v, M = 36, 60, 90
     wl = W.Workload("f32_nonfinite", 1, H, 128, 4, 1, 0, ((r_k, r_v),), F32)
-    assert lla.lib().lla_internal_f32_matrix_prefill(1, H, M, r_v) and _two_per_unit(1, H, M) == (H == 44)
+    assert lla.lib().lla_internal_f32_matrix_prefill(1, H, M, 0, r_v, 128, 0) and _two_per_unit(1, H, M) == (H == 44)
     q, ck, cv, uk, uv, muk, muv, pk, pv = _case(wl, r_k, r_v, 1, M, 0, F32)
     ref = _oracle(q, ck, cv, uk, uv, muk, muv, 0)
     cache = pk if axis == "k" else pv
@@ -123,7 +124,7 @@ def test_decode_short_contexts(r_k, r_v, N, lens, split):
     q = q[:, :, 0].contiguous()
     ws = lla.new_workspace(2, 8, r_v, N) if split else None
     log(f"decode fp32 r=({r_k},{r_v}) N={N} splits={lla.decode_splits(F32, 2, 8, N, r_k, r_v, with_workspace=split)} "
-        f"matrix={lla.lib().lla_internal_f32_matrix_decode(2, 8, N, r_v, int(split))}")
+        f"matrix={lla.lib().lla_internal_f32_matrix_decode(2, 8, N, r_v, 128, 0, int(split))}")
     for cur in (lens, lens[::-1]):
         out = lla.decode_attn(q, pk, pv, uk, uv, n_ctx=N, ctx_len=torch.tensor(cur, dtype=torch.int32, device=DEV),
                               mu_k=muk, mu_v=muv, workspace=ws)
