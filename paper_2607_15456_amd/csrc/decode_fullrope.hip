@@ -76,7 +76,8 @@ __device__ __forceinline__ f32x4 mfma16(uint4 a, uint4 b, f32x4 c) {
                                                  c, 0, 0, 0);
 }
 
-// theta of frequency f, base^(-2 f / 128).
+// theta of frequency f, base^(-2 f / 128).  A wavefront forms its 64 frequencies
+// once, one per lane, and hands them round (__shfl).
 __device__ __forceinline__ double frequency(const FullRopeArgs& a, int f) {
   return rope_frequency(a.log2_base, a.log2_base_lo, -2.0 * f / kFrD);
 }
@@ -201,7 +202,7 @@ void fullrope_mfma_kernel(FullRopeArgs a) {
   const int fq = 32 * (mt & 1) + col;
   // rope_frequency rather than pow: 8 x 4096 tokens at (192, 320) 399 -> 387 us
   // for four calls
-  const double theta_q = frequency(a, fq);
+  const double theta = frequency(a, lane), theta_q = __shfl(theta, fq);
   float q1, q2;
   {
     const bf16_t* qp = static_cast<const bf16_t*>(a.q) + bh * kFrD;
@@ -456,7 +457,7 @@ void fullrope_mfma_kernel(FullRopeArgs a) {
     }
     // the thread's frequencies are fr = tid % 32 and 32 + fr for every e
     static_assert(kFrThreads % 32 == 0, "");
-    const double th0 = frequency(a, tid & 31), th1 = frequency(a, 32 + (tid & 31));
+    const double th0 = __shfl(theta, tid & 31), th1 = __shfl(theta, 32 + (tid & 31));
     for (int e = tid; e < 2 * 32 * 32; e += kFrThreads) {
       const int hf = e >> 10, t = (e >> 5) & 31, fr = e & 31;
       float c, sn;
@@ -562,7 +563,7 @@ void fullrope_mfma_kernel(FullRopeArgs a) {
 // before, and take 54 us here (error against 64 bits 9e-7 -> 3e-7).  At r_k <= 256 the kernel above is as fast or
 // faster ((192, 320), 16 x 4096: 191 against 213 us; (96, 160): equal), each
 // LDS read of a page serving 32 rows of K rather than 16.
-// At KS >= 12 with VR = 8, and KS = 16 with VR >= 4, part of the page loads spills.
+// At KS >= 10 with VR = 8, and KS = 16 with VR >= 4, part of the page loads spills.
 // ---------------------------------------------------------------------------
 template <int KS, int VR, bool MU>
 __global__ __launch_bounds__(kFrThreads) __attribute__((amdgpu_waves_per_eu(2)))
@@ -602,9 +603,6 @@ void fullrope_rows_kernel(FullRopeArgs a) {
   const bool first_half = wave < 4;
   const int f16 = 16 * (wave & 3);  // first frequency of the M-tile
   const int hf = f16 >> 5;
-  // query rotation: lane (col, j = g & 1) forms QP for frequency f16 + col of
-  // 32-token tile j of every page
-  const double theta_q = frequency(a, f16 + col);
   float q1, q2;
   {
     const bf16_t* qp = static_cast<const bf16_t*>(a.q) + bh * kFrD;
@@ -757,6 +755,9 @@ void fullrope_rows_kernel(FullRopeArgs a) {
       }
     }
   }
+  // query rotation: lane (col, j = g & 1) forms QP for frequency f16 + col of
+  // 32-token tile j of every page (formed while the first pages are in flight)
+  const double theta = frequency(a, lane), theta_q = __shfl(theta, f16 + col);
   // Page p = pb + i.  Set (i + 1) % 2 of the key and value registers holds
   // page p + 1's keys and page p - 1's values on entry: the keys go to LDS and
   // page p + 3's are requested, the values are multiplied and page p + 1's
@@ -863,7 +864,7 @@ void fullrope_rows_kernel(FullRopeArgs a) {
   {
     // the thread's frequencies are fr = tid % 32 and 32 + fr for every e
     static_assert(kFrThreads % 32 == 0, "");
-    const double th0 = frequency(a, tid & 31), th1 = frequency(a, 32 + (tid & 31));
+    const double th0 = __shfl(theta, tid & 31), th1 = __shfl(theta, 32 + (tid & 31));
     for (int e = tid; e < 2 * 32 * 32; e += kFrThreads) {
       const int hf = e >> 10, t = (e >> 5) & 31, fr = e & 31;
       float c, sn;

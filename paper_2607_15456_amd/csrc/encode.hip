@@ -8,8 +8,10 @@
 //   B operand  = 32 tokens of x      (each token's T*d stack is contiguous),
 //   accumulator column = one token, so the 32x32 fp32 tile maps straight onto
 //   the feature-major cache page (one feature row of consecutive tokens).
-// The mean is a second accumulator fed with mu as a broadcast B operand, so
-// (x - mu) W_down is formed in fp32 without re-rounding x - mu to bf16.
+// The mean's product W_down^T mu is formed apart (a second accumulator fed with mu
+// as a broadcast B operand; in the GEMM on the vector unit from the staged
+// weights) and subtracted, so (x - mu) W_down is formed in fp32 without
+// re-rounding x - mu to bf16.
 // The pass reads x once (HBM-bound at the paper's ranks: about (r_k + r_v)/2
 // flop per byte).
 //
