@@ -381,11 +381,12 @@ __global__ __launch_bounds__(256) void encode_few_kernel(EncodeArgs a, int nrc_k
 // (workgroup i runs on XCD i % 8), so its x comes from that XCD's L2 after the
 // first read.  W_down^T mu is formed on the vector unit from the staged weights.
 // Measured against one 8-wavefront workgroup of 256 x 96 per compute unit with
-// both operands in shared LDS: 2 x 3001 tokens (192, 320) with means 227 -> 130
-// us (its bytes at the copy rate take 59), 4 x 8192 (288, 480) 1131 -> 799 us
-// (516 TFLOP/s), 300 tokens (96, 160) 35 -> 20, the LLA-2D stack (K = 8192) 2 x
-// 4096 tokens 152 -> 137 us (753 TFLOP/s).  LDS reads and the matrix units now
-// take about the same time.
+// both operands in shared LDS: 2 x 3001 tokens (192, 320) with means 216 -> 119
+// us (its bytes at the copy rate take 59), 4 x 8192 (288, 480) 950 -> 686 us (601
+// TFLOP/s), 300 tokens (96, 160) 35 -> 17, the LLA-2D stack (K = 8192) 4 x 8192
+// tokens 615 -> 484 us (852 TFLOP/s).  Bound by latency: at 2 x 3001 the vector unit
+// (epilogue, mean) is busy 33% of the time, LDS 27%, the matrix units 18%, at 2 x 4096
+// of the stack 16, 43 and 32%; wavefronts wait a third of theirs.
 constexpr int kGRow = 96, kGKC = 64, kGS = kGKC + 8;
 constexpr int kGThreads = 256;
 template <int XT>
