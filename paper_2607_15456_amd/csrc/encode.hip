@@ -731,17 +731,17 @@ __global__ __launch_bounds__(256) void encode_reduce_kernel(EncodeArgs a, int nr
 // straight from memory.  The four partial blocks add
 // through LDS in wavefront order, and a row of 32 tokens leaves as 128
 // consecutive bytes.  x - mu is formed in fp32 before the product.
-// grid: x = token block (from tb0) x row block (axis k, then v), y = head; a head's
+// grid: x = token block x row block (axis k, then v), y = head; a head's
 // workgroups on one XCD, whose L2 then holds its weights.  500 tokens of 16
 // heads, K = 512, (96, 160): 159 us with LDS-staged vector products (two LDS
 // reads per multiply-add), 37 us here (14 us of products at the matrix rate).
 constexpr int kFS = 36;  // LDS row stride of a partial block
-__global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a, int nrc_k, int nrc, int tb0) {
+__global__ __launch_bounds__(256) void encode_f32_kernel(EncodeArgs a, int nrc_k, int nrc) {
   __shared__ __attribute__((aligned(16))) float s_part[4][32 * kFS];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   int bx, h;
   xcd_head_order(bx, h, true);
-  const int tbl = (unsigned)bx / (unsigned)nrc, tb = tb0 + tbl, rc_ = bx - tbl * nrc;
+  const int tb = (unsigned)bx / (unsigned)nrc, rc_ = bx - tb * nrc;
   const int axis = rc_ >= nrc_k ? 1 : 0, rc = rc_ - axis * nrc_k;
   const int r = pick(a.r, axis), K = a.K, H = a.H, TT = a.B * a.M;
   const int c = lane & 15, g = lane >> 4;
@@ -808,11 +808,13 @@ struct GemmGrid {
     const int TT = a.B * a.M, q = 128 * XT;
     nrb_k = (a.r[0] + kGRow - 1) / kGRow;
     nrb = nrb_k + (a.r[1] + kGRow - 1) / kGRow;
-    // Blocks cut per sequence unless that adds rounds of the 8 XCDs (3 x 600
-    // tokens (240, 400) with means: 9 blocks for 8 took 88 us, 60 in one round).
+    // Blocks cut per sequence unless that adds more than an eighth to the rounds
+    // of the 8 XCDs (3 x 600 tokens (240, 400) with means: 9 blocks for 8 took 88 us,
+    // 60 in one round; 5 x 3225 of 32 heads (120, 200), K = 256: 65 for 63 299, 342
+    // over the flattened tokens, whose pieces are not whole).
     nsb = (a.M + (a.pos0 & 7) + q - 1) / q;
     ntb = (TT + q - 1) / q;
-    if (((int64_t)nsb * a.B + 7) / 8 <= (ntb + 7) / 8 * 17 / 16)
+    if (((int64_t)nsb * a.B + 7) / 8 <= (ntb + 7) / 8 * 9 / 8)
       ntb = nsb * a.B;
     else
       nsb = 0;
@@ -821,9 +823,11 @@ struct GemmGrid {
     // writes) do not pay the pipeline fill per head; 32 are for few workgroups.
     hpw = 1;
     if (XT == 2) hpw = (int)std::min<int64_t>(a.H, std::max<int64_t>(1, (int64_t)a.H * nrb * ntb / 2048));
-    // whole rounds while they are few, then half a round of slack
-    rounds = (double)((ntb + 7) / 8) * nrb * a.H / std::max(1, device_cu_count() / 4);
-    rounds = rounds < 3 ? std::ceil(rounds) : rounds + 0.5;
+    // While they are few the last round takes half a round and its share (workgroups
+    // alone on a unit run faster), the first a whole one; then half a round of slack.
+    rounds = std::max(1.0, (double)((ntb + 7) / 8) * nrb * a.H / std::max(1, device_cu_count() / 4));
+    const double whole = std::floor(rounds);
+    rounds = rounds >= 3 ? rounds + 0.5 : rounds > whole ? 0.5 * (rounds + whole + 1) : rounds;
   }
 };
 
@@ -845,9 +849,10 @@ bool gemm_ok(const EncodeArgs& a) {
   const int TT = a.B * a.M, nt = (a.r[0] + 31) / 32 + (a.r[1] + 31) / 32, nrb = GemmGrid<1>(a).nrb;
   if (TT < 192 || a.K % kGKC) return false;
   if (a.K >= 2048 && TT >= 256) return true;
+  if (a.K >= 4096) return false;
   const double mean = a.mu[0] || a.mu[1] ? 1.375 : 1.0;
   const double work = (double)((TT + kEncTok - 1) / kEncTok) * a.H * nt * (a.K + 576) * mean * nrb / (nrb + nt);
-  return work > (TT < 256 ? 486 << 10 : 195 << 10);
+  return work > (TT < 256 ? 512 << 10 : 195 << 10);
 }
 
 // 64 tokens per wavefront where 32 take more than 1.63 times the rounds (a
@@ -894,15 +899,26 @@ hipError_t launch_encode(const EncodeArgs& a, hipStream_t stream) {
   const int rmax = a.r[0] > a.r[1] ? a.r[0] : a.r[1];
   const int nrc_k = (a.r[0] + 31) / 32, nrc_v = (a.r[1] + 31) / 32;
   if (a.dtype == LLA_F32) {
-    // a launch takes fewer than 2^32 threads along x: 2^24 - 1 workgroups
-    const int nb = (TT + 31) / 32, nrc = nrc_k + nrc_v, most = ((1 << 24) - 1) / nrc;
-    hipError_t e = hipSuccess;
-    for (int tb0 = 0; tb0 < nb && e == hipSuccess; tb0 += most) {
-      dim3 grid(std::min(most, nb - tb0) * nrc, a.H);
-      hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, a, nrc_k, nrc, tb0);
-      e = hipGetLastError();
-    }
-    return e;
+    // A launch takes fewer than 2^32 threads along x, 2^24 - 1 workgroups: larger
+    // writes go out in runs of whole sequences, or of a sequence's tokens.
+    const int nrc = nrc_k + nrc_v, most = ((1 << 24) - 1) / nrc * 32;
+    const int nb = a.M <= most ? std::min(a.B, most / a.M) : 1, nm = std::min(a.M, most);
+    for (int b = 0; b < a.B; b += nb)
+      for (int m = 0; m < a.M; m += nm) {
+        EncodeArgs s = a;
+        s.B = std::min(nb, a.B - b);
+        s.M = std::min(nm, a.M - m);
+        s.pos0 = a.pos0 + m;
+        for (int i = 0; i < 2; ++i) {
+          s.x[i] = static_cast<const float*>(a.x[i]) + ((size_t)b * a.M + m) * a.H * a.K;
+          s.c[i] = static_cast<float*>(a.c[i]) + (size_t)b * a.H * a.n_max * a.r[i];
+        }
+        dim3 grid((s.B * s.M + 31) / 32 * nrc, a.H);
+        hipLaunchKernelGGL(encode_f32_kernel, grid, dim3(256), 0, stream, s, nrc_k, nrc);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
+    return hipSuccess;
   }
   const int blocks = (TT + kEncTok - 1) / kEncTok;
   switch (bf16_route(a)) {

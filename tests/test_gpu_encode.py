@@ -292,23 +292,27 @@ def test_gemm_ring(pos0):
         assert np.all(got[:, :, rest] == SENTINEL)
 
 
-def test_fp32_many_workgroups():
-    """2^27 tokens at four 32-row blocks: 2^24 workgroups of 256 threads, more than
-    a launch's x takes.  17 GB of inputs (both axes read the same) and 35 of caches."""
-    B, M, K, r = 2048, 65536, 32, 33
+@pytest.mark.parametrize("B,M", [(2048, 65536), (1, 2 ** 27 + 64)])
+def test_fp32_many_workgroups(B, M):
+    """2^27 tokens at four 32-row blocks, 2^24 workgroups of 256 threads, more than
+    a launch's x takes: whole sequences, and one.  17 GB of inputs (both axes read
+    the same) and 35 of caches."""
+    K, r = 32, 33
     if torch.cuda.mem_get_info()[0] < 80 << 30:
         pytest.skip("80 GB of free device memory")
     gen = torch.Generator(device=DEV).manual_seed(5)
     x = torch.randn((B, M, 1, K), generator=gen, device=DEV)
     wk, wv = (torch.randn((1, r, K), generator=gen, device=DEV) / K ** 0.5 for _ in range(2))
     ck, cv = (torch.full((B, 1, M // 64, r, 64), SENTINEL, device=DEV) for _ in range(2))
-    log("encode fp32 of 2^27 tokens")
+    log(f"encode fp32 of {B} x {M} tokens")
     lla.encode(x, x, wk, wv, ck, cv, T=1, pos0=0)
     torch.cuda.synchronize()
     # the first tokens, both sides of the cut between the launches, the last ones
     cut = ((1 << 24) - 1) // 4 * 32
-    for b in {0, cut // M, min(cut // M + 1, B - 1), B // 2, B - 1}:
-        for w, c in ((wk, ck), (wv, cv)):
-            ref = x[b, :, 0].double() @ w[0].double().t()
-            got = lla.from_paged(c[b:b + 1])[0, 0].double()
-            assert float((got - ref).norm() / ref.norm()) <= 1e-6
+    span = min(M, 65536)
+    for b in sorted({0, min(cut // M, B - 1), min(cut // M + 1, B - 1), B - 1}):
+        for m in sorted({0, min(cut, M - span) // 64 * 64, max(0, min(cut - span // 2, M - span)) // 64 * 64, M - span}):
+            for w, c in ((wk, ck), (wv, cv)):
+                ref = x[b, m:m + span, 0].double() @ w[0].double().t()
+                got = lla.from_paged(c[b:b + 1, :, m // 64:(m + span) // 64])[0, 0].double()
+                assert float((got - ref).norm() / ref.norm()) <= 1e-6, (b, m)
