@@ -558,9 +558,9 @@ __device__ __forceinline__ void encode_gemm_body(const EncodeArgs& a, int tfirst
       // of one feature row.  Each wavefront turns a row tile through its own
       // LDS tile [row][token]; runs of 4 lanes then store a row's tokens 16
       // bytes each where their slots are 8 consecutive ones of one sequence from
-      // a multiple of 8.  Other tokens are stored by a lane each, two rows at a
-      // time (a wavefront's stores are then two runs of consecutive slots; eight
-      // tokens by one lane in turn touched 16 rows per store).
+      // a multiple of 8.  Other tokens are stored by a lane each, two rows of 32 or
+      // more of fewer at a time (a wavefront's stores are then runs of consecutive
+      // slots; eight tokens by one lane in turn touched 16 rows per store).
       bf16_t* tile = s.tile[wave];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -596,14 +596,20 @@ __device__ __forceinline__ void encode_gemm_body(const EncodeArgs& a, int tfirst
             }
           }
           const int te = tt + col;
-          if (te >= tlo && te < thi && !whole(tt + (col & ~7), b, p)) {
-            b = te / a.M;
-            p = ring_slot(a.pos0 + (te - b * a.M), a.sink, a.window);
-            const int row0 = rw + 32 * rt + g;
-            bf16_t* dst = &cout[cache_index(b, hh, H, a.n_max, r, p, row0)];
+          const uint32_t single = (uint32_t)__builtin_amdgcn_ballot_w64(te >= tlo && te < thi &&
+                                                                        !whole(tt + (col & ~7), b, p));
+          if (single) {  // uniform; tokens first .. first + 2^sh - 1 over the lanes, 64 / 2^sh rows at a time
+            const int first = __builtin_ctz(single), n = 32 - __builtin_clz(single) - first;
+            const int sh = n > 1 ? 32 - __builtin_clz(n - 1) : 0;
+            const int tk = first + (lane & ((1 << sh) - 1));
+            if (tk < 32 && ((single >> tk) & 1)) {
+              b = (tt + tk) / a.M;
+              p = ring_slot(a.pos0 + (tt + tk - b * a.M), a.sink, a.window);
+              bf16_t* dst = &cout[cache_index(b, hh, H, a.n_max, r, p, rw + 32 * rt)];
+              const int rows = min(32, r - (rw + 32 * rt));
 #pragma unroll 4
-            for (int i = 0; i < 16; ++i)
-              if (row0 + 2 * i < r) dst[2 * i * kPage] = tile[(2 * i + g) * 40 + col];
+              for (int row = lane >> sh; row < rows; row += kWave >> sh) dst[row * kPage] = tile[row * 40 + tk];
+            }
           }
           wave_sync();
         }
